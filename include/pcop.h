@@ -117,7 +117,9 @@ typedef struct {
  *   rtol       relative residual tolerance (> 0).
  *   graph      1: run each group of Arnoldi steps as one captured HIP graph
  *              (needs a non-default stream), 0: plain launches.
- *   graph_chunk Arnoldi steps per graph launch when graph = 1 (>= 1).
+ *   graph_chunk Arnoldi steps per graph launch when graph = 1 (>= 1; whole
+ *              blocks of up to four steps that are orthogonalised together, so
+ *              at least one block).
  *   reorth_tol a second Gram-Schmidt pass is run for a member when the
  *              coefficients of the new vector against the basis exceed
  *              reorth_tol times its norm (0 = always, < 0 = never).
@@ -172,10 +174,11 @@ typedef struct {
  *   krylov_blocks  blocks per member of the Krylov reductions: 0 automatic
  *              (with tune = 1: chosen per basis size), else 1..4096 for
  *              every size (the reduction order, and so the rounding,
- *              follows it).
+ *              follows it; where Arnoldi steps are orthogonalised in blocks,
+ *              at most that many).
  *   gs_update  Gram-Schmidt update kernel: 0 automatic (with tune = 1:
  *              chosen per basis size), 1 one element per thread and step,
- *              2 double2 pairs.
+ *              2 double2 pairs (steps that are orthogonalised one by one).
  *   stream     hipStream_t on which all work is enqueued.
  *   mg_smoother  the V-cycle's Gauss-Seidel pre-smoother (PCOP_MG; Section
  *              3, Example 2 names Gauss-Seidel without an ordering): 0

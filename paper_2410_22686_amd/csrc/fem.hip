@@ -12,7 +12,7 @@
 
 namespace pcop {
 
-// y = c - s A x (c != nullptr) or y = s A x with A of eq. matrix_A (sgn = 1)
+// y = cs c - s A x (c != nullptr) or y = s A x with A of eq. matrix_A (sgn = 1)
 // or A^T (sgn = -1), E = M + tau K:
 //   y_1^j = alpha M x_1^j + sgn (E x_2^j - M x_2^{j+1}),
 //   y_2^j = alpha M x_2^j - sgn (E x_1^j - M x_1^{j-1}),  x^0 = x^{n+1} = 0.
@@ -23,7 +23,8 @@ template <int DIM, int JC>
 __global__ void __launch_bounds__(256) kkt_fem_kernel(Geo g, const double* __restrict__ x, double* __restrict__ y,
                                                       const double* __restrict__ c, const double* __restrict__ alpha,
                                                       const double* __restrict__ xscale, int xs_stride,
-                                                      const int* __restrict__ active, double sgn, int jchunk) {
+                                                      const int* __restrict__ active, double sgn, int jchunk,
+                                                          const double* __restrict__ cscale) {
   // logical block (x: spatial tile, y: time chunk, z: member) in XCD-aware
   // order, so that tiles sharing neighbour rows run on one XCD's L2
   const int total = gridDim.x * gridDim.y * gridDim.z;
@@ -42,6 +43,7 @@ __global__ void __launch_bounds__(256) kkt_fem_kernel(Geo g, const double* __res
   const Q1W w = q1_weights(nx);
   const double a = alpha[b];
   const double s = xscale ? xscale[(size_t)b * xs_stride] : 1.0;
+  const double cs = cscale ? cscale[(size_t)b * xs_stride] : 1.0;
   const size_t mb = (size_t)b * (size_t)g.vs;
   const double* x1 = x + mb;
   const double* x2 = x + mb + (size_t)n * m;
@@ -66,8 +68,8 @@ __global__ void __launch_bounds__(256) kkt_fem_kernel(Geo g, const double* __res
     r2 *= s;
     const size_t o = (size_t)j * m + i;
     if (c) {
-      r1 = cc1[o] - r1;
-      r2 = cc2[o] - r2;
+      r1 = cs * cc1[o] - r1;
+      r2 = cs * cc2[o] - r2;
     }
     y1[o] = r1;
     y2[o] = r2;
@@ -97,7 +99,8 @@ __global__ void __launch_bounds__(256) kkt_fem_lds_kernel(Geo g, const double* _
                                                           const double* __restrict__ c,
                                                           const double* __restrict__ alpha,
                                                           const double* __restrict__ xscale, int xs_stride,
-                                                          const int* __restrict__ active, double sgn, int jchunk) {
+                                                          const int* __restrict__ active, double sgn, int jchunk,
+                                                          const double* __restrict__ cscale) {
   extern __shared__ double sm[];
   const int total = gridDim.x * gridDim.y * gridDim.z;
   const int hw = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
@@ -118,6 +121,7 @@ __global__ void __launch_bounds__(256) kkt_fem_lds_kernel(Geo g, const double* _
   const Q1W w = q1_weights(nx);
   const double a = alpha[b];
   const double s = xscale ? xscale[(size_t)b * xs_stride] : 1.0;
+  const double cs = cscale ? cscale[(size_t)b * xs_stride] : 1.0;
   const size_t mb = (size_t)b * (size_t)g.vs;
   const double* x1 = x + mb;
   const double* x2 = x + mb + (size_t)n * m;
@@ -206,8 +210,8 @@ __global__ void __launch_bounds__(256) kkt_fem_lds_kernel(Geo g, const double* _
         r1 *= s;
         r2 *= s;
         if (c) {
-          r1 = cc1[o + i] - r1;
-          r2 = cc2[o + i] - r2;
+          r1 = cs * cc1[o + i] - r1;
+          r2 = cs * cc2[o + i] - r2;
         }
         y1[o + i] = r1;
         y2[o + i] = r2;
@@ -240,7 +244,8 @@ __global__ void __launch_bounds__(256) mass_apply_kernel(Geo g, const double* __
 }
 
 void launch_kkt_fem(const Geo& g, const double* x, double* y, const double* c, const double* alpha,
-                    const double* xscale, int xs_stride, const int* active, bool transpose, hipStream_t st) {
+                    const double* xscale, int xs_stride, const int* active, bool transpose, hipStream_t st,
+                    const double* cscale) {
   // 16 levels per thread with a run-time loop: unrolled 8-level chunks
   // (JC = 8) measured slower on the 2-D nx = 255, n = 255 workload
   constexpr int jc = 16;
@@ -251,11 +256,11 @@ void launch_kkt_fem(const Geo& g, const double* x, double* y, const double* c, c
     constexpr int PT = 4;
     const dim3 gl((g.m + 256 * PT - 1) / (256 * PT), (g.n + jc - 1) / jc, g.B);
     const size_t lds = 2 * sizeof(double) * (256 * PT + 2 * (size_t)(g.nx + 1));
-    kkt_fem_lds_kernel<PT><<<gl, 256, lds, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc);
+    kkt_fem_lds_kernel<PT><<<gl, 256, lds, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc, cscale);
   } else if (g.dim == 2) {
-    kkt_fem_kernel<2, 0><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc);
+    kkt_fem_kernel<2, 0><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc, cscale);
   } else {
-    kkt_fem_kernel<3, 0><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc);
+    kkt_fem_kernel<3, 0><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc, cscale);
   }
 }
 

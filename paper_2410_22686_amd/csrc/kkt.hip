@@ -7,7 +7,8 @@
 
 namespace pcop {
 
-// y = c - s A x  (c != nullptr)  or  y = s A x, with A or A^T (sgn = -1).
+// y = cs c - s A x  (c != nullptr)  or  y = s A x, with A or A^T (sgn = -1)
+// (s and cs per member, xscale and cscale with the stride xs_stride, 1 when null).
 // One thread per spatial point, marching over a chunk of time blocks so that
 // x1^{j-1} and x2^{j+1} are loaded once.  JC > 0: the chunk is JC levels, a
 // compile-time count, so the loop unrolls and the loads of every level are
@@ -17,7 +18,7 @@ __global__ void __launch_bounds__(256) kkt_apply_kernel(
     Geo g, const double* __restrict__ x, double* __restrict__ y, const double* __restrict__ c,
     const double* __restrict__ alpha, const double* __restrict__ xscale, int xs_stride,
     const int* __restrict__ active, double sgn, const double* __restrict__ ecoef, double ediag,
-    double eoff, int jchunk) {
+    double eoff, int jchunk, const double* __restrict__ cscale) {
   // logical block (x: spatial tile, y: time chunk, z: member) in XCD-friendly order
   const int total = gridDim.x * gridDim.y * gridDim.z;
   const int hw = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
@@ -34,6 +35,7 @@ __global__ void __launch_bounds__(256) kkt_apply_kernel(
   const int j1 = min(n, j0 + jchunk);
   const double a = alpha[b];
   const double s = xscale ? xscale[(size_t)b * xs_stride] : 1.0;
+  const double cs = cscale ? cscale[(size_t)b * xs_stride] : 1.0;
   const size_t mb = (size_t)b * (size_t)g.vs;
   const double* x1 = x + mb;
   const double* x2 = x + mb + (size_t)n * m;
@@ -56,8 +58,8 @@ __global__ void __launch_bounds__(256) kkt_apply_kernel(
     r1 *= s;
     r2 *= s;
     if (c) {
-      r1 = cc1[o + i] - r1;
-      r2 = cc2[o + i] - r2;
+      r1 = cs * cc1[o + i] - r1;
+      r2 = cs * cc2[o + i] - r2;
     }
     y1[o + i] = r1;
     y2[o + i] = r2;
@@ -128,7 +130,7 @@ __global__ void __launch_bounds__(256) kkt_lds_kernel(
     Geo g, const double* __restrict__ x, double* __restrict__ y, const double* __restrict__ c,
     const double* __restrict__ alpha, const double* __restrict__ xscale, int xs_stride,
     const int* __restrict__ active, double sgn, const double* __restrict__ ecoef, double ediag,
-    double eoff, int jchunk) {
+    double eoff, int jchunk, const double* __restrict__ cscale) {
   constexpr int NT = 256, TS = NT * PT;
   constexpr int QW = PT + HQ;  // staging slots per thread: TS + 2 nx <= QW NT (nx <= 128 HQ)
   extern __shared__ double kkt_sm[];
@@ -148,6 +150,7 @@ __global__ void __launch_bounds__(256) kkt_lds_kernel(
   const int j1 = min(n, j0 + jchunk);
   const double a = alpha[b];
   const double sc = xscale ? xscale[(size_t)b * xs_stride] : 1.0;
+  const double cs = cscale ? cscale[(size_t)b * xs_stride] : 1.0;
   const size_t mb = (size_t)b * (size_t)g.vs;
   const double* x1 = x + mb;
   const double* x2 = x + mb + (size_t)n * m;
@@ -186,7 +189,7 @@ __global__ void __launch_bounds__(256) kkt_lds_kernel(
   auto finish_row1 = [&](int r, int j, int i, double x2n) {
     double r1 = a * px1[r] + sgn * (pex2[r] - x2n);
     r1 *= sc;
-    if (c) r1 = cc1[(size_t)j * m + i] - r1;
+    if (c) r1 = cs * cc1[(size_t)j * m + i] - r1;
     y1[(size_t)j * m + i] = r1;
   };
   if (j0 < j1) fetch(j0);
@@ -216,7 +219,7 @@ __global__ void __launch_bounds__(256) kkt_lds_kernel(
         // block row 2: -T x1 + alpha x2
         double r2 = a * x2c - sgn * (ex1 - x1prev[r]);
         r2 *= sc;
-        if (c) r2 = cc2[o + i] - r2;
+        if (c) r2 = cs * cc2[o + i] - r2;
         y2[o + i] = r2;
         pex2[r] = ex2;
         px1[r] = x1c;
@@ -247,7 +250,7 @@ __global__ void __launch_bounds__(256) kkt_lds2_kernel(
     Geo g, const double* __restrict__ x, double* __restrict__ y, const double* __restrict__ c,
     const double* __restrict__ alpha, const double* __restrict__ xscale, int xs_stride,
     const int* __restrict__ active, double sgn, const double* __restrict__ ecoef, double ediag,
-    double eoff, int jchunk) {
+    double eoff, int jchunk, const double* __restrict__ cscale) {
   constexpr int DIM = 2, NT = 256, TS = NT * PT;
   constexpr int QW = PT + HQ;  // staging slots per thread: TS + 2 nx <= QW NT (nx <= 128 HQ)
   extern __shared__ double kkt_sm[];
@@ -268,6 +271,7 @@ __global__ void __launch_bounds__(256) kkt_lds2_kernel(
   if (j0 >= j1) return;
   const double a = alpha[b];
   const double sc = xscale ? xscale[(size_t)b * xs_stride] : 1.0;
+  const double cs = cscale ? cscale[(size_t)b * xs_stride] : 1.0;
   const size_t mb = (size_t)b * (size_t)g.vs;
   const double* x1 = x + mb;
   const double* x2 = x + mb + (size_t)n * m;
@@ -324,7 +328,7 @@ __global__ void __launch_bounds__(256) kkt_lds2_kernel(
   auto finish_row1 = [&](int r, int j, int i, double x2n) {
     double r1 = a * px1[r] + sgn * (pex2[r] - x2n);
     r1 *= sc;
-    if constexpr (RES) r1 = cc1[(size_t)j * m + i] - r1;
+    if constexpr (RES) r1 = cs * cc1[(size_t)j * m + i] - r1;
     y1[(size_t)j * m + i] = r1;
   };
   // level j's stencils; row 1 of level j - 1 is completed when FIRST is false
@@ -343,7 +347,7 @@ __global__ void __launch_bounds__(256) kkt_lds2_kernel(
       // block row 2: -T x1 + alpha x2
       double r2 = a * x2c - sgn * (ex1 - x1prev[r]);
       r2 *= sc;
-      if constexpr (RES) r2 = cc2[o + i] - r2;
+      if constexpr (RES) r2 = cs * cc2[o + i] - r2;
       y2[o + i] = r2;
       pex2[r] = ex2;
       px1[r] = x1c;
@@ -371,9 +375,10 @@ __global__ void __launch_bounds__(256) kkt_lds2_kernel(
 
 void launch_kkt_apply(const Geo& g, const double* x, double* y, const double* c, const double* alpha,
                       const double* xscale, int xs_stride, const int* active, bool transpose,
-                      const double* ecoef, double ediag, double eoff, int jchunk, hipStream_t st) {
+                      const double* ecoef, double ediag, double eoff, int jchunk, hipStream_t st,
+                      const double* cscale) {
   if (g.fem) {
-    launch_kkt_fem(g, x, y, c, alpha, xscale, xs_stride, active, transpose, st);
+    launch_kkt_fem(g, x, y, c, alpha, xscale, xs_stride, active, transpose, st, cscale);
     return;
   }
   const double sgn = transpose ? -1.0 : 1.0;
@@ -386,13 +391,13 @@ void launch_kkt_apply(const Geo& g, const double* x, double* y, const double* c,
 #define PCOP_KKT_LDS_H(D, V, HQ)                                                                                  \
   if (D == 3)                                                                                                     \
     kkt_lds_kernel<3, V, PT, HQ><<<grid, 256, lds, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, ecoef,  \
-                                                         ediag, eoff, jc);                                        \
+                                                         ediag, eoff, jc, cscale);                                        \
   else if (c)                                                                                                     \
     kkt_lds2_kernel<V, PT, HQ, true><<<grid, 256, lds, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn,     \
-                                                             ecoef, ediag, eoff, jc);                             \
+                                                             ecoef, ediag, eoff, jc, cscale);                             \
   else                                                                                                            \
     kkt_lds2_kernel<V, PT, HQ, false><<<grid, 256, lds, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn,    \
-                                                              ecoef, ediag, eoff, jc)
+                                                              ecoef, ediag, eoff, jc, cscale)
 #define PCOP_KKT_LDS(D, V)                                        \
   if (g.nx <= 256) PCOP_KKT_LDS_H(D, V, 2);                       \
   else if (g.nx <= 512) PCOP_KKT_LDS_H(D, V, 4);                  \
@@ -417,7 +422,8 @@ void launch_kkt_apply(const Geo& g, const double* x, double* y, const double* c,
   if (jchunk < 1) jchunk = 16;
   dim3 grid((g.m + 255) / 256, (g.n + jchunk - 1) / jchunk, g.B);
 #define PCOP_KKT(D, V, J) \
-  kkt_apply_kernel<D, V, J><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, ecoef, ediag, eoff, jchunk)
+  kkt_apply_kernel<D, V, J><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, ecoef, ediag, eoff, jchunk, \
+                                             cscale)
 #define PCOP_KKT_J(D, V)        \
   switch (jchunk) {             \
     case 1: PCOP_KKT(D, V, 1); break; \

@@ -90,13 +90,15 @@ struct PrecondTables {
 
 void launch_kkt_apply(const Geo& g, const double* x, double* y, const double* c, const double* alpha,
                       const double* xscale, int xs_stride, const int* active, bool transpose,
-                      const double* ecoef, double ediag, double eoff, int jchunk, hipStream_t st);
+                      const double* ecoef, double ediag, double eoff, int jchunk, hipStream_t st,
+                      const double* cscale = nullptr);
 // Q1 finite elements (fem.hip): the KKT matvec with M != I (same arguments
 // as launch_kkt_apply, which forwards to it when g.fem), and y = M x on
 // ngroups groups of spg consecutive spatial slices (group k of x at
 // k * sgs doubles, of y at k * dgs)
 void launch_kkt_fem(const Geo& g, const double* x, double* y, const double* c, const double* alpha,
-                    const double* xscale, int xs_stride, const int* active, bool transpose, hipStream_t st);
+                    const double* xscale, int xs_stride, const int* active, bool transpose, hipStream_t st,
+                    const double* cscale);
 void launch_mass_apply(const Geo& g, const double* x, long long sgs, double* y, long long dgs, int spg,
                        int ngroups, hipStream_t st);
 // dst = src or J src (flip), members at b * dvs / b * svs
@@ -167,6 +169,7 @@ struct KrylovArgs {
   int pairs;              // Gram-Schmidt update on double2 pairs (1) or doubles (0)
 };
 constexpr int kMaxBasis = 41;   // restart <= 40
+constexpr int kHld = kMaxBasis + 1;  // doubles per column of H: its entries, then the norm before the pass (blocks)
 constexpr int kRedStride = 48;  // doubles per (member, block) partial record
 
 int krylov_blocks(long long vl);
@@ -191,5 +194,29 @@ void launch_gs_step2(const double* red, int j, int B, const double* sc, double* 
 void launch_pack_hcol(const double* H, int H_ld, int j, int B, const int* skip, double* out, hipStream_t st);
 void launch_set_scale(const double* red, int col, int B, double* sc, double* norm, const int* active,
                       hipStream_t st);
+
+// Block Gram-Schmidt of S = 2..kBlockMax consecutive Krylov vectors in the
+// basis slots nv .. nv + S - 1 (krylov.hip).  Buffers per member: coef
+// [kBlockMax][kMaxBasis], beta [kBlockMax][kBlockMax], red [kBlockRed], the
+// partial sums [kBlockRed][nblk], and the record the host reads back: the
+// S columns at l kBlockCol (entries 0 .. j + 1 + l), from kBlockRecNorm the
+// norms of the vectors before the pass, at kBlockRecSkip 0 when the member
+// asks for a second pass, and from kBlockRecB scratch of the passes.
+constexpr int kBlockMax = 4;
+constexpr int kBlockRed = kBlockMax * (kMaxBasis - 1) + kBlockMax * (kBlockMax + 1) / 2;
+constexpr int kBlockCol = kMaxBasis + 1;
+constexpr int kBlockRecNorm = kBlockMax * kBlockCol;
+constexpr int kBlockRecSkip = kBlockRecNorm + kBlockMax;
+constexpr int kBlockRecB = kBlockRecSkip + 1;
+constexpr int kBlockRec = kBlockRecB + kBlockMax * kBlockMax + 3;
+constexpr int kBlockGrid = 2048;  // most blocks over all members
+int block_grid(long long vl, int B, int nv, int S);
+void launch_block_mdot(const KrylovArgs& ka, int nv, int S, double* part, int nblk, hipStream_t st);
+void launch_block_update(const KrylovArgs& ka, int nv, int S, const double* coef, const double* beta, double* part,
+                         int nblk, const int* skip, hipStream_t st);
+void launch_block_reduce(const double* part, int nblk, int nv, int S, int B, double* out, hipStream_t st);
+void launch_block_step(const double* red, int j, int S, int pass, int B, double* sc, double* H, int H_ld,
+                       double* coef, double* beta, double* rec, double reorth_tol, int* skip, const int* active,
+                       hipStream_t st);
 
 }  // namespace pcop

@@ -165,12 +165,14 @@ struct Layout {
   int M = 1;
   int RC = 0;  // Rader convolution length of a prime-factor plan, or 0
   size_t sc, H, coef, red, partial, wnorm2, norm, skip, active, finish, hcol;
+  size_t bcoef, bbeta, bred, bpart, brec;  // block Gram-Schmidt (krylov.hip)
   size_t basis, zbasis, tmp1, tmp2, xpad, spec;
   size_t mgcoef[kMaxMgLevels], mgz[kMaxMgLevels], mgr[kMaxMgLevels];
   int mg_levels = 0;
   int mg_nx[kMaxMgLevels];
   int nblk = 1;      // default blocks per member of the Krylov reductions
   int nblk_max = 1;  // the most the partial-sum buffer holds (tuner candidates)
+  int nblk_blk = 1;  // the most blocks per member of the block Gram-Schmidt kernels
   long long vl = 0;
   long long vs = 0;  // member stride of the solver's vectors: vl padded to 256 bytes
 };
@@ -223,9 +225,9 @@ void plan_layout(const pcop_problem* p, const pcop_options* o, Layout& L) {
   L.sg = take(L, sizeof(double) * B);
   L.ecoef = (p->coeff_kind == PCOP_COEFF_HALFGRID) ? take(L, sizeof(double) * (1 + 2 * d) * m) : 0;
   L.sc = take(L, sizeof(double) * B * kMaxBasis);
-  L.H = take(L, sizeof(double) * B * (kMaxBasis - 1) * kMaxBasis);
+  L.H = take(L, sizeof(double) * B * (kMaxBasis - 1) * kHld);
   L.coef = take(L, sizeof(double) * B * kMaxBasis);
-  L.red = take(L, sizeof(double) * B * kRedStride);
+  L.red = take(L, sizeof(double) * 2 * B * kRedStride);
   L.partial = take(L, sizeof(double) * B * (size_t)L.nblk_max * kRedStride);
   L.wnorm2 = take(L, sizeof(double) * B);
   L.norm = take(L, sizeof(double) * B);
@@ -233,6 +235,12 @@ void plan_layout(const pcop_problem* p, const pcop_options* o, Layout& L) {
   L.active = take(L, sizeof(int) * B);
   L.finish = take(L, sizeof(int) * B);
   L.hcol = take(L, sizeof(double) * B * (kMaxBasis + 1));
+  L.nblk_blk = block_grid(L.vl, B, 1, 2);  // the most of any basis size
+  L.bcoef = take(L, sizeof(double) * B * kBlockMax * kMaxBasis);
+  L.bbeta = take(L, sizeof(double) * B * kBlockMax * kBlockMax);
+  L.bred = take(L, sizeof(double) * B * kBlockRed);
+  L.bpart = take(L, sizeof(double) * B * (size_t)L.nblk_blk * kBlockRed);
+  L.brec = take(L, sizeof(double) * B * kBlockRec);
   L.vs = (L.vl + 31) / 32 * 32;
   const size_t vec = sizeof(double) * (size_t)L.vs * B;
   L.basis = take(L, vec * (o->restart + 1));
@@ -370,16 +378,16 @@ struct pcop_ctx_s {
   // pinned host staging for every scalar transfer of the solver
   double* pin = nullptr;
   double* pin_col = nullptr;    // [B][kMaxBasis]  Hessenberg column
-  double* pin_sc = nullptr;     // [B][kMaxBasis]  basis scales
+  double* pin_rec = nullptr;    // [B][kBlockRec]  block Gram-Schmidt records
   double* pin_coef = nullptr;   // [B][kMaxBasis]  combination coefficients
-  double* pin_red = nullptr;    // [B][kRedStride] reductions
-  double* pin_H = nullptr;      // [B][kMaxBasis - 1][kMaxBasis] Hessenberg (graph mode)
+  double* pin_red = nullptr;    // [2][B][kRedStride] reductions (the solve's last residual, the right-hand side)
+  double* pin_H = nullptr;      // [B][kMaxBasis - 1][kHld] Hessenberg (graph mode)
   double* pin_norm = nullptr;   // [B]
   int* pin_active = nullptr;    // [B]
   int* pin_finish = nullptr;    // [B]
   // HIP graphs of Arnoldi chunks (graph = 1): captured on a private stream
   hipStream_t gst = nullptr;
-  std::vector<std::pair<int, hipGraphExec_t>> graphs;  // key j0 * 64 + count
+  std::vector<std::pair<int, hipGraphExec_t>> graphs;  // key (j0 * 64 + count) * 8 + block length
   ~pcop_ctx_s() {
     for (auto& g : graphs) (void)hipGraphExecDestroy(g.second);
     if (gst) (void)hipStreamDestroy(gst);
@@ -428,10 +436,10 @@ pcop_status do_precond(pcop_ctx c, const double* v, double* w, const double* vsc
 }
 
 void do_kkt(pcop_ctx c, const double* x, double* y, const double* cvec, const double* xscale, int xs_stride,
-            const int* mask, int nact) {
+            const int* mask, int nact, const double* cscale = nullptr) {
   tbeg(c->kt(), KF_KKT, (cvec ? 24.0 : 16.0) * c->g.vl * nact);
   launch_kkt_apply(c->g, x, y, cvec, c->at<double>(c->L.alpha), xscale, xs_stride, mask, false, c->ecoef,
-                   c->ediag, c->eoff, c->kkt_jchunk, c->st);
+                   c->ediag, c->eoff, c->kkt_jchunk, c->st, cscale);
   tend(c->kt());
 }
 
@@ -456,11 +464,11 @@ void do_update(pcop_ctx c, const KrylovArgs& ka, int nv, double* w, const int* s
   tend(c->kt());
 }
 
-// squared norms of member vectors (into red[b][0])
-void do_norm2(pcop_ctx c, const double* w, const int* mask, int nact) {
+// squared norms of member vectors (into out[b][0])
+void do_norm2(pcop_ctx c, const double* w, const int* mask, int nact, double* out) {
   KrylovArgs ka = c->kargs(c->basis(0), mask);
   do_mdot(c, ka, 0, w, nact);
-  launch_reduce_partials(c->at<double>(c->L.partial), c->nb_mdot[0], 1, c->g.B, c->at<double>(c->L.red), c->st);
+  launch_reduce_partials(c->at<double>(c->L.partial), c->nb_mdot[0], 1, c->g.B, out, c->st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1095,7 +1103,7 @@ pcop_status pcop_setup(pcop_ctx* out, const pcop_problem* prob, const pcop_optio
   }
 
   {
-    const size_t nd = (size_t)B * (3 * kMaxBasis + 1 + kRedStride + 1 + (kMaxBasis - 1) * kMaxBasis) +
+    const size_t nd = (size_t)B * (2 * kMaxBasis + 1 + kBlockRec + 2 * kRedStride + 1 + (kMaxBasis - 1) * kHld) +
                       2 * (size_t)B + 8;
     hipError_t pe = hipHostMalloc(reinterpret_cast<void**>(&c->pin), nd * sizeof(double), hipHostMallocDefault);
     if (pe != hipSuccess) {
@@ -1105,14 +1113,14 @@ pcop_status pcop_setup(pcop_ctx* out, const pcop_problem* prob, const pcop_optio
     double* q = c->pin;
     c->pin_col = q;
     q += (size_t)B * (kMaxBasis + 1);
-    c->pin_sc = q;
-    q += (size_t)B * kMaxBasis;
+    c->pin_rec = q;
+    q += (size_t)B * kBlockRec;
     c->pin_coef = q;
     q += (size_t)B * kMaxBasis;
     c->pin_red = q;
-    q += (size_t)B * kRedStride;
+    q += 2 * (size_t)B * kRedStride;
     c->pin_H = q;
-    q += (size_t)B * (kMaxBasis - 1) * kMaxBasis;
+    q += (size_t)B * (kMaxBasis - 1) * kHld;
     c->pin_norm = q;
     q += B;
     c->pin_active = reinterpret_cast<int*>(q);
@@ -1450,39 +1458,120 @@ pcop_status pcop_timing_read(pcop_ctx c, pcop_kernel_stat* out, int cap, int* co
 // ---------------------------------------------------------------------------
 namespace {
 
-// Enqueue Arnoldi step j on stream st: operator, first Gram-Schmidt pass,
-// measured orthogonality, and (full = true) the member-masked second pass.
-pcop_status enqueue_iteration(pcop_ctx c, int j, bool full, int n_active, hipStream_t st) {
+// Krylov vectors per block: the longest run of operator applies without an
+// orthogonalisation in between (krylov.hip).  Rounding in the operator and in
+// the Gram-Schmidt pass counts relative to the share of a vector that the pass
+// leaves.  With the shift of block_shifted that share was 1e-3 to 0.06 at worst
+// over four steps, for gamma from 1e-10 to 1, and the iterates agree with
+// single steps to 1e-15 (as two orders of summation do); without it to 1e-14
+// over four and three times less over two steps, so the left side, where the
+// shift would cost passes of its own, takes two.  FP32 V-cycles agree to 4e-13.
+// The FP32 sine transforms are exact solves but for their rounding, which then
+// sets the last steps of a solve to 1e-8 (two-step blocks moved those
+// residuals by up to a quarter): single steps.
+int block_limit(pcop_ctx c) {
+  if (c->fp32 && c->opt.spatial == PCOP_DST) return 1;
+  return c->opt.side == PCOP_LEFT ? 2 : kBlockMax;
+}
+
+// A vector is used only while the ratio of the one before it stays above
+// this; below it the block is cut and the cycle goes on in single steps.
+constexpr double kBlockMinRatio = 1e-6;
+
+// Whether step l of a block of S stores u - Op u instead of Op u.  The
+// preconditioned spectrum lies around 1 (Re = 1 for the ideal preconditioner),
+// so this takes the vector's own direction out of what the next step applies
+// the operator to, for one more read in the matvec (its residual form).
+bool block_shifted(pcop_ctx c, int l, int S) { return c->opt.side != PCOP_LEFT && l + 1 < S; }
+
+// w = Op u (or u - Op u, block_shifted) for Krylov step j + l of the block
+// of S that starts at j: u is basis vector j (l = 0) or the vector w of the
+// step before, not orthogonalised
+pcop_status enqueue_operator(pcop_ctx c, int j, int l, int S, int n_active) {
+  double* tmp1 = c->at<double>(c->L.tmp1);
+  int* active = c->at<int>(c->L.active);
+  const double* u = c->basis(j + l);
+  double* w = c->basis(j + l + 1);
+  const double* scale = l == 0 ? c->at<double>(c->L.sc) + j : nullptr;  // member stride kMaxBasis
+  pcop_status s = PCOP_OK;
+  if (c->opt.side == PCOP_LEFT) {
+    do_kkt(c, u, tmp1, nullptr, scale, kMaxBasis, active, n_active);
+    s = do_precond(c, tmp1, w, nullptr, 0, 0, active, n_active);
+  } else {
+    double* z = c->opt.side == PCOP_FLEXIBLE ? c->zbasis(j + l) : tmp1;
+    s = do_precond(c, u, z, scale, kMaxBasis, 0, active, n_active);
+    const bool shift = block_shifted(c, l, S);
+    do_kkt(c, z, w, shift ? u : nullptr, nullptr, kMaxBasis, active, n_active, scale);
+  }
+  return s;
+}
+
+// blocks per member of the block kernels, within the caller's krylov_blocks
+int block_count(pcop_ctx c, int nv, int S) {
+  const int nb = block_grid(c->g.vl, c->g.B, nv, S);
+  return c->opt.krylov_blocks > 0 ? std::min(nb, c->opt.krylov_blocks) : nb;
+}
+
+// second Gram-Schmidt pass of the block at j for the members with skip = 0
+void enqueue_block_again(pcop_ctx c, int j, int S, int nact, hipStream_t st) {
   const Layout& L = c->L;
   const int B = c->g.B;
-  double* tmp1 = c->at<double>(L.tmp1);
+  int* active = c->at<int>(L.active);
+  int* skip = c->at<int>(L.skip);
+  double* red = c->at<double>(L.bred);
+  double* part = c->at<double>(L.bpart);
+  const int nb = block_count(c, j + 1, S);
+  KrylovArgs ka = c->kargs(c->basis(0), active);
+  tbeg(c->kt(), KF_UPDATE, 8.0 * (j + 1 + 2 * S) * c->g.vl * nact);
+  launch_block_update(ka, j + 1, S, c->at<double>(L.bcoef), c->at<double>(L.bbeta), part, nb, skip, st);
+  tend(c->kt());
+  launch_block_reduce(part, nb, j + 1, S, B, red, st);
+  launch_block_step(red, j, S, 2, B, c->at<double>(L.sc), c->at<double>(L.H), kHld, c->at<double>(L.bcoef),
+                    c->at<double>(L.bbeta), c->at<double>(L.brec), c->opt.reorth_tol, skip, active, st);
+}
+
+// Enqueue the S Arnoldi steps j .. j + S - 1 on stream st: operators, one
+// Gram-Schmidt pass over the block, measured orthogonality, and (full = true)
+// the member-masked second pass.
+pcop_status enqueue_block(pcop_ctx c, int j, int S, bool full, int n_active, hipStream_t st) {
+  const Layout& L = c->L;
+  const int B = c->g.B;
   double* sc = c->at<double>(L.sc);
   double* H = c->at<double>(L.H);
+  int* skip = c->at<int>(L.skip);
+  int* active = c->at<int>(L.active);
+  const int H_ld = kHld;
+  for (int l = 0; l < S; ++l) {
+    pcop_status s = enqueue_operator(c, j, l, S, n_active);
+    if (s != PCOP_OK) return s;
+  }
+  KrylovArgs ka = c->kargs(c->basis(0), active);
+  if (S > 1) {
+    double* red = c->at<double>(L.bred);
+    double* part = c->at<double>(L.bpart);
+    double* coef = c->at<double>(L.bcoef);
+    double* beta = c->at<double>(L.bbeta);
+    double* rec = c->at<double>(L.brec);
+    const int nv = j + 1, nb = block_count(c, nv, S);
+    tbeg(c->kt(), KF_MDOT, 8.0 * (nv + S) * c->g.vl * n_active);
+    launch_block_mdot(ka, nv, S, part, nb, st);
+    tend(c->kt());
+    launch_block_reduce(part, nb, nv, S, B, red, st);
+    launch_block_step(red, j, S, 0, B, sc, H, H_ld, coef, beta, rec, c->opt.reorth_tol, skip, active, st);
+    tbeg(c->kt(), KF_UPDATE, 8.0 * (nv + 2 * S) * c->g.vl * n_active);
+    launch_block_update(ka, nv, S, coef, beta, part, nb, nullptr, st);
+    tend(c->kt());
+    launch_block_reduce(part, nb, nv, S, B, red, st);
+    launch_block_step(red, j, S, 1, B, sc, H, H_ld, coef, beta, rec, c->opt.reorth_tol, skip, active, st);
+    if (full) enqueue_block_again(c, j, S, n_active, st);
+    return PCOP_OK;
+  }
+  // one vector: classical Gram-Schmidt; the update pass also measures it
   double* coef = c->at<double>(L.coef);
   double* red = c->at<double>(L.red);
   double* partial = c->at<double>(L.partial);
   double* wnorm2 = c->at<double>(L.wnorm2);
-  int* skip = c->at<int>(L.skip);
-  int* active = c->at<int>(L.active);
-  const int H_ld = kMaxBasis;
-  double* vj = c->basis(j);
   double* w = c->basis(j + 1);
-  const double* scj = sc + j;  // member stride kMaxBasis
-  pcop_status s = PCOP_OK;
-  const int side = c->opt.side;
-  if (side == PCOP_RIGHT) {
-    s = do_precond(c, vj, tmp1, scj, kMaxBasis, 0, active, n_active);
-    do_kkt(c, tmp1, w, nullptr, nullptr, 0, active, n_active);
-  } else if (side == PCOP_FLEXIBLE) {
-    s = do_precond(c, vj, c->zbasis(j), scj, kMaxBasis, 0, active, n_active);
-    do_kkt(c, c->zbasis(j), w, nullptr, nullptr, 0, active, n_active);
-  } else {
-    do_kkt(c, vj, tmp1, nullptr, scj, kMaxBasis, active, n_active);
-    s = do_precond(c, tmp1, w, nullptr, 0, 0, active, n_active);
-  }
-  if (s != PCOP_OK) return s;
-  // classical Gram-Schmidt; the update pass also measures the new vector
-  KrylovArgs ka = c->kargs(c->basis(0), active);
   do_mdot(c, ka, j + 1, w, n_active);
   launch_reduce_partials(partial, c->nb_mdot[j + 1], j + 2, B, red, st);
   launch_gs_step1(red, j, B, sc, H, H_ld, coef, kMaxBasis, wnorm2, active, st);
@@ -1497,9 +1586,10 @@ pcop_status enqueue_iteration(pcop_ctx c, int j, bool full, int n_active, hipStr
   return PCOP_OK;
 }
 
-// The graph for Arnoldi steps j0 .. j0 + cnt - 1 (captured on first use).
-pcop_status chunk_graph(pcop_ctx c, int j0, int cnt, hipGraphExec_t* out) {
-  const int key = j0 * 64 + cnt;
+// The graph for Arnoldi steps j0 .. j0 + cnt - 1 in blocks of S (captured on
+// first use).
+pcop_status chunk_graph(pcop_ctx c, int j0, int cnt, int S, hipGraphExec_t* out) {
+  const int key = (j0 * 64 + cnt) * 8 + S;
   for (auto& g : c->graphs)
     if (g.first == key) {
       *out = g.second;
@@ -1511,7 +1601,8 @@ pcop_status chunk_graph(pcop_ctx c, int j0, int cnt, hipGraphExec_t* out) {
   c->st = c->gst;
   PCOP_HIP(hipStreamBeginCapture(c->gst, hipStreamCaptureModeThreadLocal));
   pcop_status s = PCOP_OK;
-  for (int j = j0; j < j0 + cnt && s == PCOP_OK; ++j) s = enqueue_iteration(c, j, true, c->g.B, c->gst);
+  for (int j = j0; j < j0 + cnt && s == PCOP_OK; j += S)
+    s = enqueue_block(c, j, std::min(S, j0 + cnt - j), true, c->g.B, c->gst);
   hipGraph_t graph = nullptr;
   hipError_t e = hipStreamEndCapture(c->gst, &graph);
   c->st = saved;
@@ -1539,7 +1630,33 @@ struct MemberState {
   // Givens data of the current cycle
   double cs[kMaxBasis], sn[kMaxBasis], gv[kMaxBasis + 1];
   double R[kMaxBasis - 1][kMaxBasis];  // rotated columns
+  // the vector whose operator image column jj holds, in the orthonormal
+  // basis (entries 0 .. jj): basis vector jj at the start of a block, the
+  // column before it inside one
+  double U[kMaxBasis - 1][kMaxBasis];
+  double est_block = 1.0;  // est at the end of the block before the last
 };
+
+// steps of the next block: the fewest that the members' last convergence
+// rate says are left (rounded up, the mean over the members: a step too many
+// costs an operator apply, a block too short streams the basis once more),
+// within limit
+int block_length(const std::vector<MemberState>& ms, const std::vector<int>& h_active, double rtol, int limit,
+                 int last) {
+  double need = 0.0;
+  int cnt = 0;
+  for (size_t m = 0; m < ms.size(); ++m) {
+    if (!h_active[m]) continue;
+    const MemberState& s = ms[m];
+    double r = limit;
+    if (last > 0 && s.est > rtol && s.est < s.est_block)
+      r = std::min<double>(limit, std::ceil(last * std::log(s.est / rtol) / std::log(s.est_block / s.est)));
+    need += r;
+    ++cnt;
+  }
+  if (cnt == 0) return limit;
+  return std::max(1, std::min(limit, (int)std::ceil(need / cnt)));
+}
 
 // solve the upper-triangular k x k system of the rotated Hessenberg
 void back_substitute(const MemberState& s, int k, double* y) {
@@ -1592,7 +1709,7 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
   int* skip = c->at<int>(L.skip);
   int* active = c->at<int>(L.active);
   int* finish = c->at<int>(L.finish);
-  const int H_ld = kMaxBasis;
+  const int H_ld = kHld;
 
   // the solve runs on padded copies of b and x (member stride g.vs);
   // A^T = J A J: solve A z = J b and return x = J z
@@ -1604,18 +1721,20 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
   std::vector<MemberState> ms(B);
   std::vector<int> h_active(B, 1), h_finish(B, 0);
   std::vector<double> h_norm(B), h_col((size_t)B * (kMaxBasis + 1)), h_coef((size_t)B * kMaxBasis);
-  std::vector<double> bnorm(B), h_sc((size_t)B * kMaxBasis);
-  const size_t H_member = (size_t)(kMaxBasis - 1) * kMaxBasis;
+  std::vector<double> h_sc((size_t)B * kMaxBasis), h_rec((size_t)B * kBlockRec);
+  const size_t H_member = (size_t)(kMaxBasis - 1) * H_ld;
   std::vector<double> h_H(use_graph ? (size_t)B * H_member : 0);
   double* hcol = c->at<double>(L.hcol);
   // Every host<->device transfer goes through pinned staging; an upload
-  // buffer is only rewritten after a stream synchronisation.
-  bool pending = false;
+  // buffer is only rewritten after a stream synchronisation (the
+  // coefficients' one is: a download lies between two of its uploads).
+  bool pending_active = false, pending_finish = false;
   auto sync = [&]() -> hipError_t {
-    pending = false;
+    pending_active = pending_finish = false;
     return hipStreamSynchronize(st);
   };
   auto upload_ints = [&](int* dev, const std::vector<int>& src, int* pinbuf) -> hipError_t {
+    bool& pending = pinbuf == c->pin_active ? pending_active : pending_finish;
     if (pending) {
       hipError_t e = sync();
       if (e != hipSuccess) return e;
@@ -1630,13 +1749,10 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
     if (e == hipSuccess) std::memcpy(host, pinbuf, sizeof(double) * count);
     return e;
   };
-  std::vector<double> h_red((size_t)B * kRedStride);
+  std::vector<double> h_red((size_t)2 * B * kRedStride);
 
-  // ||b|| for the final true residual
-  PCOP_HIP(upload_ints(active, h_active, c->pin_active));
-  do_norm2(c, bb, nullptr, B);
-  PCOP_HIP(download(h_red.data(), red, c->pin_red, (size_t)B * kRedStride));
-  for (int m = 0; m < B; ++m) bnorm[m] = std::sqrt(h_red[(size_t)m * kRedStride]);
+  // ||b|| for the final true residual (read back with it)
+  do_norm2(c, bb, nullptr, B, red + (size_t)B * kRedStride);
 
   bool first_cycle = true;
   pcop_status result = PCOP_OK;
@@ -1688,40 +1804,83 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
     if (n_active == 0) break;
     PCOP_HIP(upload_ints(active, h_active, c->pin_active));
 
+    for (int m = 0; m < B; ++m) {
+      h_sc[(size_t)m * kMaxBasis] = h_norm[m] > 0.0 ? 1.0 / h_norm[m] : 0.0;
+      ms[m].est_block = ms[m].est;
+    }
+
     int j = 0;
+    int last = 0;                   // steps of the block before, 0 at the start of a cycle
+    int limit = block_limit(c);     // 1 once a block had to be cut
     while (j < restart) {
       n_active = 0;
-      for (int m = 0; m < B; ++m) n_active += h_active[m];
-      int cnt = 1;
+      int left = restart - j;
+      for (int m = 0; m < B; ++m) {
+        n_active += h_active[m];
+        if (h_active[m]) left = std::min(left, std::max(1, maxit - ms[m].iters));
+      }
+      const int S = block_length(ms, h_active, rtol, std::min(limit, left), last);
+      int cnt = S;
       if (use_graph) {
-        // a chunk of Arnoldi steps as one graph; members that converge inside
-        // the chunk run to its end and their extra steps are ignored
-        cnt = std::min(c->opt.graph_chunk, restart - j);
+        // a chunk of Arnoldi steps as one graph, whole blocks of it; members
+        // that converge inside the chunk run to its end and their extra steps
+        // are ignored
+        cnt = S * std::max(1, std::min(c->opt.graph_chunk, restart - j) / S);
         hipGraphExec_t ge = nullptr;
-        pcop_status gs = chunk_graph(c, j, cnt, &ge);
+        pcop_status gs = chunk_graph(c, j, cnt, S, &ge);
         if (gs != PCOP_OK) return gs;
         PCOP_HIP(hipGraphLaunch(ge, st));
         PCOP_HIP(download(h_H.data(), H, c->pin_H, (size_t)B * H_member));
       } else {
-        pcop_status s = enqueue_iteration(c, j, false, n_active, st);
+        pcop_status s = enqueue_block(c, j, S, false, n_active, st);
         if (s != PCOP_OK) return s;
-        // column j of H for every member, with the flag for a second pass
-        launch_pack_hcol(H, H_ld, j, B, skip, hcol, st);
-        PCOP_HIP(download(h_col.data(), hcol, c->pin_col, (size_t)B * (kMaxBasis + 1)));
+        // the block's columns of H for every member, with the flag for a second pass
+        auto read = [&]() -> hipError_t {
+          if (S > 1) return download(h_rec.data(), c->at<double>(L.brec), c->pin_rec, (size_t)B * kBlockRec);
+          launch_pack_hcol(H, H_ld, j, B, skip, hcol, st);
+          return download(h_col.data(), hcol, c->pin_col, (size_t)B * (kMaxBasis + 1));
+        };
+        PCOP_HIP(read());
         int n_again = 0;
-        for (int m = 0; m < B; ++m)
-          if (h_active[m] && h_col[(size_t)m * (kMaxBasis + 1) + kMaxBasis] == 0.0) ++n_again;
+        for (int m = 0; m < B; ++m) {
+          const double flag = S > 1 ? h_rec[(size_t)m * kBlockRec + kBlockRecSkip]
+                                    : h_col[(size_t)m * (kMaxBasis + 1) + kMaxBasis];
+          if (h_active[m] && flag == 0.0) ++n_again;
+        }
         if (n_again > 0) {
           // second classical Gram-Schmidt pass for the members that need it
-          KrylovArgs ka = c->kargs(c->basis(0), active);
-          do_update(c, ka, j + 1, c->basis(j + 1), skip, n_again);
-          launch_reduce_partials(partial, c->nb_upd[j + 1], j + 2, B, red, st);
-          launch_gs_step2(red, j, B, sc, H, H_ld, coef, kMaxBasis, wnorm2, c->opt.reorth_tol, skip, sc, active, 1,
-                          st);
-          launch_pack_hcol(H, H_ld, j, B, skip, hcol, st);
-          PCOP_HIP(download(h_col.data(), hcol, c->pin_col, (size_t)B * (kMaxBasis + 1)));
+          if (S > 1) {
+            enqueue_block_again(c, j, S, n_again, st);
+          } else {
+            KrylovArgs ka = c->kargs(c->basis(0), active);
+            do_update(c, ka, j + 1, c->basis(j + 1), skip, n_again);
+            launch_reduce_partials(partial, c->nb_upd[j + 1], j + 2, B, red, st);
+            launch_gs_step2(red, j, B, sc, H, H_ld, coef, kMaxBasis, wnorm2, c->opt.reorth_tol, skip, sc, active, 1,
+                            st);
+          }
+          PCOP_HIP(read());
         }
       }
+      // the measured column jj of member m and, inside a block, the norm of
+      // its vector before the Gram-Schmidt pass
+      auto column = [&](int m, int jj) -> const double* {
+        if (use_graph) return &h_H[(size_t)m * H_member + (size_t)jj * H_ld];
+        if (S > 1) return &h_rec[(size_t)m * kBlockRec + (size_t)(jj - j) * kBlockCol];
+        return &h_col[(size_t)m * (kMaxBasis + 1)];
+      };
+      // a block is cut behind the first vector that the Gram-Schmidt pass
+      // left nothing of: the vectors built on it say nothing new
+      for (int l = 0; l + 1 < cnt && S > 1; ++l) {
+        if ((l + 1) % S == 0) continue;  // the next column starts a block of its own
+        for (int m = 0; m < B; ++m) {
+          if (!h_active[m]) continue;
+          const double* col = column(m, j + l);
+          const double before = use_graph ? col[kHld - 1] : h_rec[(size_t)m * kBlockRec + kBlockRecNorm + l];
+          if (!(col[j + l + 1] > kBlockMinRatio * before)) cnt = std::min(cnt, l + 1);
+        }
+      }
+      const bool cut = cnt % S != 0;
+      if (cut) limit = 1;
       // Givens rotations of the new columns; a member ends its cycle at the
       // first step that converges, exhausts maxit or reaches the restart
       bool any_finish = false;
@@ -1733,13 +1892,23 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
         MemberState& ms_ = ms[m];
         if (!h_active[m]) continue;
         for (int jj = j; jj < j + cnt; ++jj) {
-          double colbuf[kMaxBasis + 1];
-          double* col = colbuf;
-          if (use_graph) {
-            const double* src = &h_H[(size_t)m * H_member + (size_t)jj * H_ld];
+          double col[kMaxBasis + 1];
+          {
+            const double* src = column(m, jj);
             for (int i = 0; i <= jj + 1; ++i) col[i] = src[i];
-          } else {
-            col = &h_col[(size_t)m * (kMaxBasis + 1)];
+            h_sc[(size_t)m * kMaxBasis + jj + 1] = col[jj + 1] > 0.0 ? 1.0 / col[jj + 1] : 0.0;
+            if ((jj - j) % S == 0) {
+              for (int i = 0; i <= jj; ++i) ms_.U[jj][i] = i == jj ? 1.0 : 0.0;
+            } else {
+              const double* before = column(m, jj - 1);
+              for (int i = 0; i <= jj; ++i) ms_.U[jj][i] = before[i];
+            }
+            if ((jj - j) % S == 0) ms_.est_block = ms_.est;
+            // Op u = u - w where the step stored w = u - Op u
+            if (block_shifted(c, (jj - j) % S, S)) {
+              for (int i = 0; i <= jj; ++i) col[i] = ms_.U[jj][i] - col[i];
+              col[jj + 1] = -col[jj + 1];
+            }
           }
           for (int i = 0; i < jj; ++i) {
             const double t = ms_.cs[i] * col[i] + ms_.sn[i] * col[i + 1];
@@ -1775,18 +1944,25 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
           }
         }
       }
+      last = cut ? cnt % S : S;
       j += cnt;
       if (!any_finish) continue;
       // form the correction for the members that end their cycle here
       std::fill(h_coef.begin(), h_coef.end(), 0.0);
-      PCOP_HIP(download(h_sc.data(), sc, c->pin_sc, (size_t)B * kMaxBasis));
       for (int m = 0; m < B; ++m) {
         if (!h_finish[m]) continue;
         const int k = kfin[m];
         double y[kMaxBasis];
         back_substitute(ms[m], k, y);
-        for (int i = 0; i < k; ++i)
-          h_coef[(size_t)m * kMaxBasis + i] = (side == PCOP_FLEXIBLE) ? y[i] : y[i] * h_sc[(size_t)m * kMaxBasis + i];
+        for (int i = 0; i < k; ++i) {
+          if (side == PCOP_FLEXIBLE) {
+            h_coef[(size_t)m * kMaxBasis + i] = y[i];
+            continue;
+          }
+          double v = 0.0;  // the operators' arguments in the orthonormal basis
+          for (int q = i; q < k; ++q) v += ms[m].U[q][i] * y[q];
+          h_coef[(size_t)m * kMaxBasis + i] = v * h_sc[(size_t)m * kMaxBasis + i];
+        }
       }
       std::memcpy(c->pin_coef, h_coef.data(), sizeof(double) * B * kMaxBasis);
       PCOP_HIP(hipMemcpyAsync(coef, c->pin_coef, sizeof(double) * B * kMaxBasis, hipMemcpyHostToDevice, st));
@@ -1822,21 +1998,20 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
     }
   }
 
-  // true residual ||b - A x|| / ||b||
-  std::fill(h_active.begin(), h_active.end(), 1);
-  PCOP_HIP(upload_ints(active, h_active, c->pin_active));
+  // true residual ||b - A x|| / ||b||, every member
   do_kkt(c, x, tmp1, bb, nullptr, 0, nullptr, B);
-  do_norm2(c, tmp1, nullptr, B);
+  do_norm2(c, tmp1, nullptr, B, red);
   launch_restride(g, x, g.vs, xu, g.vl, transpose != 0, st);
-  PCOP_HIP(download(h_red.data(), red, c->pin_red, (size_t)B * kRedStride));
+  PCOP_HIP(download(h_red.data(), red, c->pin_red, 2 * (size_t)B * kRedStride));
   PCOP_HIP(hipGetLastError());
   for (int m = 0; m < B; ++m) {
     const double rt = std::sqrt(h_red[(size_t)m * kRedStride]);
+    const double bnorm = std::sqrt(h_red[(size_t)(B + m) * kRedStride]);
     if (info) {
       info[m].iters = ms[m].iters;
       info[m].converged = ms[m].converged ? 1 : 0;
       info[m].relres_est = ms[m].est;
-      info[m].relres_true = bnorm[m] > 0.0 ? rt / bnorm[m] : rt;
+      info[m].relres_true = bnorm > 0.0 ? rt / bnorm : rt;
     }
     if (!ms[m].converged) result = PCOP_NOT_CONVERGED;
   }
