@@ -877,6 +877,29 @@ static bool dst_pass(const Geo& g, cx<T>* data, const LineGeom& lg, bool rows, b
   }
 }
 
+// the passes of nslices spatial slices: contiguous x1 rows; x2 lines in planes
+// (slice, x3), 3-D only as an outer axis; the last axis, one plane per slice
+struct SliceLines {
+  LineGeom rows, ax2, last;
+};
+static SliceLines slice_lines(const Geo& g, long long nslices) {
+  const int nx = g.nx, inner = g.dim == 3 ? nx * nx : nx;
+  return SliceLines{LineGeom{1, 0, (int)(nslices * inner), nx, 1}, LineGeom{nslices * nx, (long long)nx * nx, nx, 1, nx},
+                    LineGeom{nslices, (long long)g.m, inner, 1, inner}};
+}
+
+// (-1/(2(nx+1)))^d: the factor of a forward and an inverse transform over all
+// axes, (-2i)^{2d}, against the orthonormal one
+double dst_norm(const Geo& g) {
+  return (g.dim == 2) ? 1.0 / (4.0 * (g.nx + 1.0) * (g.nx + 1.0))
+                      : -1.0 / (8.0 * (g.nx + 1.0) * (g.nx + 1.0) * (g.nx + 1.0));
+}
+
+template <class T>
+static const cx<T>* dst_twiddles(const PrecondTables& tb) {
+  return reinterpret_cast<const cx<T>*>(sizeof(T) == 8 ? (const void*)tb.twL64 : (const void*)tb.twL32);
+}
+
 // Step 2 with sine transforms: axes 1..d-1 forward, last axis forward +
 // divide + inverse, axes d-1..1 inverse (the transforms commute).  spm
 // slices per member; slice q of member b is divided by
@@ -884,20 +907,9 @@ static bool dst_pass(const Geo& g, cx<T>* data, const LineGeom& lg, bool rows, b
 template <class T>
 static bool dst_solve(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm, const double* lam,
                       hipStream_t st) {
-  const int nx = g.nx;
-  const long long slices = (long long)g.B * spm;
-  DivideParams dp{tb.mu1, lam, tb.alpha, tb.active, 0.0, spm, tb.im1};
-  dp.cnorm = (g.dim == 2) ? 1.0 / (4.0 * (nx + 1.0) * (nx + 1.0))
-                          : -1.0 / (8.0 * (nx + 1.0) * (nx + 1.0) * (nx + 1.0));
-  const cx<T>* twL = reinterpret_cast<const cx<T>*>(sizeof(T) == 8 ? (const void*)tb.twL64 : (const void*)tb.twL32);
-  // x1: contiguous rows
-  LineGeom rows{1, 0, (int)(slices * (g.dim == 3 ? nx * nx : nx)), nx, 1};
-  // x2 (3-D only as an outer axis): planes (b, q, x3), lines x1, stride nx
-  LineGeom ax2{slices * nx, (long long)nx * nx, nx, 1, nx};
-  // last axis with the division: planes (b, q), lines = nx^{d-1}
-  const int lines_last = (g.dim == 3) ? nx * nx : nx;
-  const int stride_last = (g.dim == 3) ? nx * nx : nx;
-  LineGeom last{slices, (long long)g.m, lines_last, 1, stride_last};
+  const DivideParams dp{tb.mu1, lam, tb.alpha, tb.active, dst_norm(g), spm, tb.im1};
+  const cx<T>* twL = dst_twiddles<T>(tb);
+  const SliceLines sl = slice_lines(g, (long long)g.B * spm);
   // every pass reads and writes the slices of the counted members once
   const double pass_bytes = 2.0 * sizeof(cx<T>) * spm * (double)g.m * tb.nact;
   bool ok = true;
@@ -907,12 +919,39 @@ static bool dst_solve(const Geo& g, cx<T>* spec, const PrecondTables& tb, int sp
     ok = dst_pass<T>(g, spec, lg, r, dv, twL, dp, tb.dst_variant, tb.ncu, st);
     tend(tb.timer);
   };
-  run(rows, true, false, KF_DST_ROWS);
-  if (g.dim == 3) run(ax2, false, false, KF_DST_AX2);
-  run(last, false, true, KF_DST_LAST);
-  if (g.dim == 3) run(ax2, false, false, KF_DST_AX2);
-  run(rows, true, false, KF_DST_ROWS);
+  run(sl.rows, true, false, KF_DST_ROWS);
+  if (g.dim == 3) run(sl.ax2, false, false, KF_DST_AX2);
+  run(sl.last, false, true, KF_DST_LAST);
+  if (g.dim == 3) run(sl.ax2, false, false, KF_DST_AX2);
+  run(sl.rows, true, false, KF_DST_ROWS);
   return ok;
+}
+
+// the sine transform over every axis of the nslices slices at data, in place
+// and unnormalised (dst_norm)
+template <class T>
+static bool dst_transform(const Geo& g, cx<T>* data, const PrecondTables& tb, long long nslices, hipStream_t st) {
+  const DivideParams dp{tb.mu1, nullptr, nullptr, nullptr, 1.0, 1, nullptr};
+  const cx<T>* twL = dst_twiddles<T>(tb);
+  const SliceLines sl = slice_lines(g, nslices);
+  const double pass_bytes = 2.0 * sizeof(cx<T>) * nslices * (double)g.m;
+  bool ok = true;
+  auto run = [&](const LineGeom& lg, bool r, int fam) {
+    if (!ok) return;
+    tbeg(tb.timer, fam, pass_bytes);
+    ok = dst_pass<T>(g, data, lg, r, false, twL, dp, tb.dst_variant, tb.ncu, st);
+    tend(tb.timer);
+  };
+  run(sl.rows, true, KF_DST_ROWS);
+  if (g.dim == 3) run(sl.ax2, false, KF_DST_AX2);
+  run(sl.last, false, KF_DST_LAST);
+  return ok;
+}
+
+bool launch_dst_transform(const Geo& g, void* data, bool fp32, const PrecondTables& tb, long long nslices,
+                          hipStream_t st) {
+  if (fp32) return dst_transform<float>(g, reinterpret_cast<cx<float>*>(data), tb, nslices, st);
+  return dst_transform<double>(g, reinterpret_cast<cx<double>*>(data), tb, nslices, st);
 }
 
 bool launch_dst_solve(const Geo& g, void* spec, bool fp32, const PrecondTables& tb, int spm, const double* lam,

@@ -129,7 +129,12 @@ bool launch_mg_solve(const Geo& g, void* spec, bool fp32, const PrecondTables& t
                      hipStream_t st);
 bool launch_dst_solve(const Geo& g, void* spec, bool fp32, const PrecondTables& tb, int spm, const double* lam,
                       hipStream_t st);
-// ideal RBD preconditioner (sequential in time); unit = device (1.0, 0.0);
+// the sine transform over every axis of nslices consecutive complex slices, in
+// place; a second one times dst_norm(g) inverts it
+bool launch_dst_transform(const Geo& g, void* data, bool fp32, const PrecondTables& tb, long long nslices,
+                          hipStream_t st);
+double dst_norm(const Geo& g);
+// ideal RBD preconditioner; unit = device (1.0, 0.0);
 // uses ideal_spec_bytes(g, fp32) bytes of spec
 bool launch_ideal_precond(const Geo& g, const double* v, double* w, void* spec, bool fp32, int spatial,
                           const PrecondTables& tb, const double* unit, const double* vscale, int vs_stride,
