@@ -223,6 +223,163 @@ __global__ void __launch_bounds__(256) kkt_fem_lds_kernel(Geo g, const double* _
   }
 }
 
+// 3-D version with LDS tiles.  A block owns 16 x 16 x TZ points (one thread
+// per (x1, x2), TZ points along x3) and marches over a chunk of levels; per
+// level the boxes of x_1^j and x_2^{j+1} around its points (one point of halo
+// on every side, zeros outside the grid) are staged in LDS while the next
+// level's are fetched into registers.  A thread reads the 3 x 3 neighbours of
+// each plane once and adds the plane's x1-x2 sums to the three outputs it
+// belongs to: 9 (TZ + 2)/TZ LDS reads per point and field instead of 27 loads
+// through the vector cache, which bound the global-memory kernel.  TZ = 4 takes
+// 208 registers (two waves per SIMD); with TZ = 8 the unrolled planes spill.
+// Same operations per point as kkt_fem_kernel<3>.  nx = 63, n = 63: 735 -> 176
+// us per launch (0.69 -> 2.9 TB/s of its bytes), nx = 31, n = 99, two members:
+// 278 -> 74 us; without the register prefetch of the next level 193 and 78.
+// Below nx = 15 most of a tile would lie outside the grid.
+constexpr int kFemTz = 4;
+template <int TZ, bool RES>
+__global__ void __launch_bounds__(256) kkt_fem3_lds_kernel(Geo g, const double* __restrict__ x, double* __restrict__ y,
+                                                           const double* __restrict__ c,
+                                                           const double* __restrict__ alpha,
+                                                           const double* __restrict__ xscale, int xs_stride,
+                                                           const int* __restrict__ active, double sgn, int jchunk,
+                                                           const double* __restrict__ cscale, Q1W w) {
+  constexpr int TX = 16, SX = TX + 2, SP = SX * SX, SEG = SP * (TZ + 2);
+  constexpr int NS = (SEG + 255) / 256;
+  __shared__ double s1[SEG], s2[SEG];
+  const int total = gridDim.x * gridDim.y * gridDim.z;
+  const int hw = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  const int lg = xcd_remap(hw, total);
+  const int bx = lg % gridDim.x;
+  const int by = (lg / gridDim.x) % gridDim.y;
+  const int b = lg / (gridDim.x * gridDim.y);
+  if (active && !active[b]) return;
+  const int nx = g.nx, n = g.n, m = g.m;
+  const int tiles = (nx + TX - 1) / TX;
+  const int x0 = bx % tiles * TX, y0 = bx / tiles % tiles * TX, z0 = bx / (tiles * tiles) * TZ;
+  const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
+  const int j0 = by * jchunk;
+  const int j1 = min(n, j0 + jchunk);
+  const double a = alpha[b];
+  const double s = xscale ? xscale[(size_t)b * xs_stride] : 1.0;
+  const double cs = cscale ? cscale[(size_t)b * xs_stride] : 1.0;
+  const size_t mb = (size_t)b * (size_t)g.vs;
+  const double* x1 = x + mb;
+  const double* x2 = x + mb + (size_t)n * m;
+  double* y1 = y + mb;
+  double* y2 = y + mb + (size_t)n * m;
+  const double* cc1 = RES ? c + mb : nullptr;
+  const double* cc2 = RES ? c + mb + (size_t)n * m : nullptr;
+  // the grid point of each of this thread's staging slots, -1 outside the grid
+  int gi[NS];
+#pragma unroll
+  for (int q = 0; q < NS; ++q) {
+    const int t = threadIdx.x + 256 * q;
+    const int px = x0 - 1 + t % SX, py = y0 - 1 + t / SX % SX, pz = z0 - 1 + t / SP;
+    const bool in = t < SEG && px >= 0 && px < nx && py >= 0 && py < nx && pz >= 0 && pz < nx;
+    gi[q] = in ? px + nx * (py + nx * pz) : -1;
+  }
+  // unconditional loads from clamped points and levels; the zeros outside the
+  // grid and past the last level are put in at the commit
+  double p1[NS], p2[NS];
+  auto fetch = [&](int l1, int l2) {
+    const double* a1 = x1 + (size_t)max(l1, 0) * m;
+    const double* a2 = x2 + (size_t)min(l2, n - 1) * m;
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+      p1[q] = a1[max(gi[q], 0)];
+      p2[q] = a2[max(gi[q], 0)];
+    }
+  };
+  auto commit = [&](bool has1, bool has2) {
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+      if (q < NS - 1 || threadIdx.x + 256 * q < SEG) {
+        s1[threadIdx.x + 256 * q] = gi[q] >= 0 && has1 ? p1[q] : 0.0;
+        s2[threadIdx.x + 256 * q] = gi[q] >= 0 && has2 ? p2[q] : 0.0;
+      }
+  };
+  // M u and K u at the thread's TZ points
+  auto stencil = [&](const double* sg, double (&Mu)[TZ], double (&Ku)[TZ]) {
+    // opaque, so that the read addresses are formed here and not kept over
+    // the level loop (36 registers)
+    int lb = ty * SX + tx;
+    asm("" : "+v"(lb));
+#pragma unroll
+    for (int z = 0; z < TZ; ++z) Mu[z] = Ku[z] = 0.0;
+#pragma unroll
+    for (int pz = 0; pz < TZ + 2; ++pz) {
+      double Qm = 0.0, Qk = 0.0;
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) {
+        const double* r = sg + lb + pz * SP + dy * SX;
+        const double ul = r[0], uc = r[1], ur = r[2];
+        const double rm = w.m0 * uc + w.m1 * (ul + ur);
+        const double rk = w.k0 * uc + w.k1 * (ul + ur);
+        const double my = dy == 1 ? w.m0 : w.m1, ky = dy == 1 ? w.k0 : w.k1;
+        Qm += my * rm;
+        Qk += my * rk + ky * rm;
+      }
+      // plane pz lies one behind, at and one ahead of points pz, pz - 1, pz - 2
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const int z = pz - d;
+        if (z >= 0 && z < TZ) {
+          const double mz = d == 1 ? w.m0 : w.m1, kz = d == 1 ? w.k0 : w.k1;
+          Mu[z] += mz * Qm;
+          Ku[z] += mz * Qk + kz * Qm;
+        }
+      }
+    }
+  };
+  double Mx1prev[TZ], Mx2c[TZ], Ex2c[TZ];  // E = M + tau K
+  fetch(j0 - 1, j0);
+  commit(j0 > 0, true);
+  __syncthreads();
+  fetch(j0, j0 + 1);
+  {
+    double K[TZ];
+    stencil(s1, Mx1prev, K);
+    stencil(s2, Mx2c, K);
+#pragma unroll
+    for (int z = 0; z < TZ; ++z) Ex2c[z] = Mx2c[z] + g.tau * K[z];
+  }
+  const int px = x0 + tx, py = y0 + ty;
+  const bool own = px < nx && py < nx;
+  const int zn = min(TZ, nx - z0);
+  const size_t pi = (size_t)px + (size_t)nx * (py + (size_t)nx * z0);
+  for (int j = j0; j < j1; ++j) {
+    __syncthreads();
+    commit(true, j + 1 < n);
+    __syncthreads();
+    if (j + 1 < j1) fetch(j + 1, j + 2);
+    const size_t o = (size_t)j * m + pi;
+    double M[TZ], K[TZ], r[TZ];
+    // row 2 from the x_1 box, then row 1 from the x_2 box
+    stencil(s1, M, K);
+#pragma unroll
+    for (int z = 0; z < TZ; ++z) {
+      r[z] = s * (a * Mx2c[z] - sgn * (M[z] + g.tau * K[z] - Mx1prev[z]));
+      Mx1prev[z] = M[z];
+    }
+    if (own)
+#pragma unroll
+      for (int z = 0; z < TZ; ++z)
+        if (z < zn) y2[o + (size_t)z * nx * nx] = RES ? cs * cc2[o + (size_t)z * nx * nx] - r[z] : r[z];
+    stencil(s2, M, K);
+#pragma unroll
+    for (int z = 0; z < TZ; ++z) {
+      r[z] = s * (a * Mx1prev[z] + sgn * (Ex2c[z] - M[z]));
+      Mx2c[z] = M[z];
+      Ex2c[z] = M[z] + g.tau * K[z];
+    }
+    if (own)
+#pragma unroll
+      for (int z = 0; z < TZ; ++z)
+        if (z < zn) y1[o + (size_t)z * nx * nx] = RES ? cs * cc1[o + (size_t)z * nx * nx] - r[z] : r[z];
+  }
+}
+
 // y = M x on spatial slices: slice q of group k = q / spg starts at
 // x + k sgs + (q mod spg) m and y + k dgs + (q mod spg) m
 template <int DIM>
@@ -246,19 +403,32 @@ __global__ void __launch_bounds__(256) mass_apply_kernel(Geo g, const double* __
 void launch_kkt_fem(const Geo& g, const double* x, double* y, const double* c, const double* alpha,
                     const double* xscale, int xs_stride, const int* active, bool transpose, hipStream_t st,
                     const double* cscale) {
-  // 16 levels per thread with a run-time loop: unrolled 8-level chunks
-  // (JC = 8) measured slower on the 2-D nx = 255, n = 255 workload
-  constexpr int jc = 16;
+  // levels per block: 16 with a run-time loop (unrolled 8-level chunks, JC = 8,
+  // measured slower on the 2-D nx = 255, n = 255 workload), fewer where that
+  // leaves fewer than 1024 blocks: a chunk of jc levels reads jc + 1
+  auto chunk = [&](long long blocks) {
+    int jc = 16;
+    while (jc > 1 && blocks * ((g.n + jc - 1) / jc) * g.B < 1024) jc /= 2;
+    return jc;
+  };
+  int jc = chunk((g.m + 255) / 256);
   const dim3 grid((g.m + 255) / 256, (g.n + jc - 1) / jc, g.B);
   const double sgn = transpose ? -1.0 : 1.0;
   if (g.dim == 2 && g.nx <= 511) {
     // LDS tiles (the prefetch slots cover a halo of up to 512 points)
     constexpr int PT = 4;
+    jc = chunk((g.m + 256 * PT - 1) / (256 * PT));
     const dim3 gl((g.m + 256 * PT - 1) / (256 * PT), (g.n + jc - 1) / jc, g.B);
     const size_t lds = 2 * sizeof(double) * (256 * PT + 2 * (size_t)(g.nx + 1));
     kkt_fem_lds_kernel<PT><<<gl, 256, lds, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc, cscale);
   } else if (g.dim == 2) {
     kkt_fem_kernel<2, 0><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc, cscale);
+  } else if (g.nx >= 15) {
+    const int t16 = (g.nx + 15) / 16, tz = (g.nx + kFemTz - 1) / kFemTz;
+    jc = chunk((long long)t16 * t16 * tz);
+    const dim3 gl(t16 * t16 * tz, (g.n + jc - 1) / jc, g.B);
+    auto kernel = c ? kkt_fem3_lds_kernel<kFemTz, true> : kkt_fem3_lds_kernel<kFemTz, false>;
+    kernel<<<gl, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc, cscale, q1_weights(g.nx));
   } else {
     kkt_fem_kernel<3, 0><<<grid, 256, 0, st>>>(g, x, y, c, alpha, xscale, xs_stride, active, sgn, jc, cscale);
   }
