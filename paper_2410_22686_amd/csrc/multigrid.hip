@@ -360,10 +360,8 @@ __global__ void __launch_bounds__(256) mg_prolong_kernel(int nxf, int mf, int nx
       cw[a][0] = (T)1;
       cw[a][1] = (T)0;
     } else {
-      // (nxc = 0 on a one-point grid, where the launch only copies: every
-      // weight is then zero and every index 0, still a valid address)
       ci[a][0] = I >= 1 ? I - 1 : 0;
-      ci[a][1] = I < nxc ? I : (nxc > 0 ? nxc - 1 : 0);
+      ci[a][1] = I < nxc ? I : nxc - 1;
       cw[a][0] = I >= 1 ? (T)0.5 : (T)0;
       cw[a][1] = I < nxc ? (T)0.5 : (T)0;
     }
@@ -490,6 +488,308 @@ __global__ void __launch_bounds__(256) mg_residual_full_kernel(int nx, int m, in
   }
 }
 
+// ---------------------------------------------------------------------------
+// Two-dimensional lexicographic sweeps by one wave per slice.  Lane t owns
+// column x1 = t (from the other end for the backward sweep) and walks along
+// x2, one step behind its neighbour: the point it handles at step w lies on
+// the hyperplane x1 + x2 = w, its new x1-neighbour is what lane t - 1 computed
+// at the step before (a lane shift) and its new x2-neighbour is its own last
+// value, so no barrier and no memory lies between two hyperplanes.  What does
+// not depend on the sweep (right-hand side, coefficients, reciprocal of |d|^2,
+// in the backward sweep the old neighbours) is read kSweepAhead steps ahead.
+// C > 1: a lane owns C neighbouring columns, updated one after another.
+// What bounds a sweep is the chain of 2 nx - 1 updates (nx + 64 steps of C) and
+// the 64 lines per load that the skewed accesses touch (eight steps ahead
+// instead of four changed nothing).  FP64, one member, nt = 64, symmetric
+// sweeps, one apply: nx = 127 1165 -> 403 us, nx = 255 (nt = 32) 2552 -> 1461.
+// ---------------------------------------------------------------------------
+constexpr int kSweepAhead = 4;
+
+// the value of the lane below (0 in lane 0)
+__device__ __forceinline__ float lane_below(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ double lane_below(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true));
+}
+
+// r and z: one slice, in LDS or global memory
+template <class T, int C, bool BACK, class RP, class ZP>
+__device__ __forceinline__ void sweep_columns(int nx, int m, const T* __restrict__ coef, const RP r, ZP z,
+                                              cx<T> sig) {
+  const int t = threadIdx.x & (kWave - 1);
+  const int last = (nx + C - 1) / C - 1;  // lane of the last column
+  // step w of lane t: row w - t (counted from the far end when BACK)
+  auto point = [&](int w, int u) {
+    const int e = C * t + u, row = min(max(w - t, 0), nx - 1);
+    const int x1 = min(e, nx - 1);
+    return BACK ? (nx - 1 - x1) + nx * (nx - 1 - row) : x1 + nx * row;
+  };
+  struct Pre {
+    cx<T> a;      // right-hand side, less the old neighbours' part when BACK
+    T o1, o2;     // couplings to the neighbour columns / rows already done
+    T dx, rd;     // Re d and 1 / |d|^2
+  };
+  auto fetch = [&](int w, Pre (&q)[C]) {
+#pragma unroll
+    for (int u = 0; u < C; ++u) {
+      const int i = point(w, u);
+      q[u].a = r[i];
+      q[u].dx = sig.x + coef[i];
+      q[u].rd = recip(q[u].dx * q[u].dx + sig.y * sig.y);
+      q[u].o1 = coef[(size_t)(BACK ? 2 : 1) * m + i];
+      q[u].o2 = coef[(size_t)(BACK ? 4 : 3) * m + i];
+      if (BACK) {
+        // minus neighbours, not yet updated (zero coupling where outside)
+        const T b1 = coef[(size_t)m + i], b2 = coef[(size_t)3 * m + i];
+        q[u].a = q[u].a - scale(z[max(i - 1, 0)], b1);
+        q[u].a = q[u].a - scale(z[max(i - nx, 0)], b2);
+      }
+    }
+  };
+  cx<T> own[C];
+#pragma unroll
+  for (int u = 0; u < C; ++u) own[u] = cx<T>{0, 0};
+  auto step = [&](int w, Pre (&q)[C]) {
+    const int row = w - t;
+    const bool in = row >= 0 && row < nx && t <= last;
+    cx<T> side{lane_below(own[C - 1].x), lane_below(own[C - 1].y)};
+#pragma unroll
+    for (int u = 0; u < C; ++u) {
+      cx<T> a = q[u].a - scale(side, q[u].o1);
+      a = a - scale(own[u], q[u].o2);
+      const cx<T> v{(a.x * q[u].dx + a.y * sig.y) * q[u].rd, (a.y * q[u].dx - a.x * sig.y) * q[u].rd};
+      own[u] = in ? v : cx<T>{0, 0};
+      if (in && C * t + u < nx) z[point(w, u)] = own[u];
+      side = own[u];
+    }
+  };
+  Pre q[kSweepAhead][C];
+#pragma unroll
+  for (int k = 0; k < kSweepAhead; ++k) fetch(k, q[k]);
+  const int steps = nx + last;
+  for (int w = 0; w < steps; w += kSweepAhead) {
+#pragma unroll
+    for (int k = 0; k < kSweepAhead; ++k) {
+      step(w + k, q[k]);
+      fetch(w + k + kSweepAhead, q[k]);
+    }
+  }
+}
+
+template <class T, int C>
+__global__ void __launch_bounds__(kWave) mg_sweep_columns_kernel(int nx, int m, const T* __restrict__ coef,
+                                                                 const cx<T>* __restrict__ r, cx<T>* z, MgShift sh,
+                                                                 int back) {
+  const int s = blockIdx.x;
+  if (sh.active && !sh.active[s / sh.twoK]) return;
+  const cx<T> sig = slice_sigma<T>(sh, s);
+  const cx<T>* rs = r + (size_t)s * m;
+  cx<T>* zs = z + (size_t)s * m;
+  if (back) sweep_columns<T, C, true>(nx, m, coef, rs, zs, sig);
+  else sweep_columns<T, C, false>(nx, m, coef, rs, zs, sig);
+}
+
+// ---------------------------------------------------------------------------
+// The cycle's coarse end in one launch: a block takes one slice through every
+// level from the first that fits LDS (2-D nx <= 63, 3-D nx <= 15) down to one
+// point and back up.  Level by level these were three or four launches each of
+// a few microseconds' work (and one block per slice of dependent hyperplanes
+// for the lexicographic sweeps).  The level below the first keeps its
+// correction where the first level's residual was, which its restriction has
+// consumed.  Operations per point as in the kernels above.
+// What bounds it is latency: one block per slice, a barrier per phase.  One
+// apply, 64 slices, before and now: 2-D nx = 63 FP64 red-black 78 -> 54 us,
+// lexicographic 248 -> 83, symmetric 472 -> 129; with 16 times the slices
+// (FP64, one block per CU) 260 -> 261, 473 -> 380, 845 -> 565; 3-D nx = 15,
+// two members, 69 -> 58, 141 -> 99, 253 -> 167.
+// ---------------------------------------------------------------------------
+constexpr int kTailThreads = 512;
+constexpr size_t kTailLds = 160 * 1024 - 1024;
+
+template <class T>
+struct MgTail {
+  int levels;
+  int nx[kMaxMgLevels];
+  const T* coef[kMaxMgLevels];
+};
+
+template <class T, int DIM>
+__global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, const cx<T>* rin, cx<T>* out, MgShift sh,
+                                                               int smoother) {
+  extern __shared__ __align__(16) unsigned char tail_sm[];
+  const int s = blockIdx.x;
+  if (sh.active && !sh.active[s / sh.twoK]) return;
+  const cx<T> sig = slice_sigma<T>(sh, s);
+  cx<T>* const base = reinterpret_cast<cx<T>*>(tail_sm);
+  const int tid = threadIdx.x;
+  auto points = [](int nx) { return DIM == 3 ? nx * nx * nx : nx * nx; };
+  const int m0 = points(lv.nx[0]);
+  // z of the first level, its right-hand side (and later the corrections of
+  // the coarser levels), the coarser right-hand sides
+  cx<T>* z = base;
+  cx<T>* r = base + m0;
+  cx<T>* znext = base + m0;
+  cx<T>* rnext = base + 2 * m0;
+  for (int i = tid; i < m0; i += kTailThreads) r[i] = rin[(size_t)s * m0 + i];
+  __syncthreads();
+  for (int l = 0; l < lv.levels; ++l) {
+    const int nx = lv.nx[l], m = points(nx);
+    const T* __restrict__ coef = lv.coef[l];
+    if (smoother == 0) {
+      for (int i = tid; i < m; i += kTailThreads) {
+        int c[3];
+        coords(i, nx, DIM, c);
+        cx<T> acc = r[i];
+        if (((c[0] + c[1] + c[2]) & 1) != 0) {
+          int stride = 1;
+#pragma unroll
+          for (int a = 0; a < DIM; ++a) {
+            if (c[a] > 0)
+              acc = acc - scale(cdiv(r[i - stride], cx<T>{sig.x + coef[i - stride], sig.y}), coef[(size_t)(1 + 2 * a) * m + i]);
+            if (c[a] < nx - 1)
+              acc = acc - scale(cdiv(r[i + stride], cx<T>{sig.x + coef[i + stride], sig.y}), coef[(size_t)(2 + 2 * a) * m + i]);
+            stride *= nx;
+          }
+        }
+        z[i] = cdiv(acc, cx<T>{sig.x + coef[i], sig.y});
+      }
+    } else if (DIM == 2) {
+      if (tid < kWave) {
+        sweep_columns<T, 1, false>(nx, m, coef, r, z, sig);
+        if (smoother == 2) {
+          // one wave's LDS accesses complete in order
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+          sweep_columns<T, 1, true>(nx, m, coef, r, z, sig);
+        }
+      }
+    } else {
+      const int top = DIM * (nx - 1);
+      for (int pass = 0; pass < smoother; ++pass) {
+        for (int st = 0; st <= top; ++st) {
+          const int w = pass ? top - st : st;
+          const int x3lo = max(0, w - 2 * (nx - 1)), x3hi = min(w, nx - 1);
+          for (int t = tid; t < (x3hi - x3lo + 1) * nx; t += kTailThreads) {
+            const int x3 = x3lo + t / nx, x1 = t % nx, x2 = w - x3 - x1;
+            if (x2 < 0 || x2 >= nx) continue;
+            const int c[3] = {x1, x2, x3};
+            const int i = x1 + nx * (x2 + nx * x3);
+            cx<T> acc = r[i];
+            int stride = 1;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+              if (c[a] > 0) acc = acc - scale(z[i - stride], coef[(size_t)(1 + 2 * a) * m + i]);
+              if (pass && c[a] < nx - 1) acc = acc - scale(z[i + stride], coef[(size_t)(2 + 2 * a) * m + i]);
+              stride *= nx;
+            }
+            z[i] = cdiv(acc, cx<T>{sig.x + coef[i], sig.y});
+          }
+          __syncthreads();
+        }
+      }
+    }
+    __syncthreads();
+    if (l + 1 == lv.levels) break;
+    // residual over the consumed right-hand side (red-black: the red points)
+    for (int i = tid; i < m; i += kTailThreads) {
+      int c[3];
+      coords(i, nx, DIM, c);
+      cx<T> acc{0, 0};
+      if (smoother == 0) {
+        if (((c[0] + c[1] + c[2]) & 1) != 0) continue;
+      } else {
+        const T dx = sig.x + coef[i];
+        const cx<T> zi = z[i];
+        acc = r[i] - cx<T>{dx * zi.x - sig.y * zi.y, dx * zi.y + sig.y * zi.x};
+      }
+      int stride = 1;
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) {
+        if (c[a] > 0) acc = acc - scale(z[i - stride], coef[(size_t)(1 + 2 * a) * m + i]);
+        if (c[a] < nx - 1) acc = acc - scale(z[i + stride], coef[(size_t)(2 + 2 * a) * m + i]);
+        stride *= nx;
+      }
+      r[i] = acc;
+    }
+    __syncthreads();
+    const int nxc = lv.nx[l + 1], mc = points(nxc);
+    for (int I = tid; I < mc; I += kTailThreads) {
+      int C[3];
+      coords(I, nxc, DIM, C);
+      cx<T> acc{0, 0};
+      const int o2 = (DIM == 3) ? 1 : 0;
+      for (int d2 = -o2; d2 <= o2; ++d2)
+        for (int d1 = -1; d1 <= 1; ++d1)
+          for (int d0 = -1; d0 <= 1; ++d0) {
+            const int f0 = 2 * C[0] + 1 + d0, f1 = 2 * C[1] + 1 + d1, f2 = (DIM == 3) ? 2 * C[2] + 1 + d2 : 0;
+            if (smoother == 0 && ((f0 + f1 + f2) & 1) != 0) continue;
+            const T w = (d0 == 0 ? (T)1 : (T)0.5) * (d1 == 0 ? (T)1 : (T)0.5) * (d2 == 0 ? (T)1 : (T)0.5);
+            acc = acc + scale(r[f0 + nx * (f1 + nx * f2)], w);
+          }
+      rnext[I] = scale(acc, (DIM == 3) ? (T)0.125 : (T)0.25);
+    }
+    __syncthreads();
+    z = znext;
+    znext += mc;
+    r = rnext;
+    rnext += mc;
+  }
+  // z is the coarsest correction; the finer ones lie before it
+  for (int l = lv.levels - 2; l >= 0; --l) {
+    const int nx = lv.nx[l], m = points(nx), nxc = lv.nx[l + 1];
+    cx<T>* zf = l == 0 ? base : z - m;
+    for (int i = tid; i < m; i += kTailThreads) {
+      int f[3];
+      coords(i, nx, DIM, f);
+      int ci[DIM][2];
+      T cw[DIM][2];
+#pragma unroll
+      for (int a = 0; a < DIM; ++a) {
+        const int I = f[a] >> 1;
+        const bool on = f[a] & 1;
+        ci[a][0] = on ? I : max(I - 1, 0);
+        ci[a][1] = on ? I : min(I, nxc - 1);
+        cw[a][0] = on ? (T)1 : (I >= 1 ? (T)0.5 : (T)0);
+        cw[a][1] = on ? (T)0 : (I < nxc ? (T)0.5 : (T)0);
+      }
+      cx<T> acc = zf[i];
+#pragma unroll
+      for (int u = 0; u < (1 << DIM); ++u) {
+        int I = 0, stride = 1;
+        T wt = (T)1;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+          const int b = (u >> a) & 1;
+          I += ci[a][b] * stride;
+          wt *= cw[a][b];
+          stride *= nxc;
+        }
+        acc = acc + scale(z[I], wt);
+      }
+      zf[i] = acc;
+    }
+    __syncthreads();
+    z = zf;
+  }
+  for (int i = tid; i < m0; i += kTailThreads) out[(size_t)s * m0 + i] = base[i];
+}
+
+// first level of the one-launch coarse end: its two planes and the coarser
+// right-hand sides fit LDS, and a 2-D column per lane
+template <class T, int DIM>
+static int tail_level(const PrecondTables& tb, size_t* lds) {
+  for (int l = 0; l < tb.mg_levels; ++l) {
+    size_t pts = tb.mg[l].m;
+    for (int k = l; k < tb.mg_levels; ++k) pts += tb.mg[k].m;
+    *lds = pts * sizeof(cx<T>);
+    if (*lds <= kTailLds && tb.mg[l].nx <= kWave) return l;
+  }
+  return tb.mg_levels;
+}
+
 // slices per thread of the smoother, the residual and the prolongation on
 // levels where that still gives at least kMgMinBlocks blocks (one slice per
 // thread below)
@@ -528,15 +828,27 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
     const int np = m / nx * ((nx + 1) / 2);
     return dim3((np + 255) / 256, (slices + sb - 1) / sb);
   };
-  for (int l = 0; l < NL; ++l) {
+  // levels from lt on in one launch (one point at the latest)
+  size_t tail_lds = 0;
+  const int lt = tail_level<T, DIM>(tb, &tail_lds);
+  for (int l = 0; l < lt; ++l) {
     const int nx = tb.mg[l].nx;
     const int m = (int)tb.mg[l].m;
     const dim3 gridb = grid_sb(m);
     tbeg(tb.timer, KF_MG_SMOOTH, 2.0 * cs * m);
     if (lex) {
-      mg_sweep_lex_kernel<T, DIM, false><<<slices, 256, 0, st>>>(nx, m, coefp(l), rbuf(l), zbuf(l), sh);
-      if (tb.mg_smoother == 2)
-        mg_sweep_lex_kernel<T, DIM, true><<<slices, 256, 0, st>>>(nx, m, coefp(l), rbuf(l), zbuf(l), sh);
+      for (int back = 0; back < tb.mg_smoother; ++back) {
+        // one wave per slice up to four columns per lane; wider grids walk
+        // the hyperplanes with a block
+        if (DIM == 2 && nx <= 2 * kWave)
+          mg_sweep_columns_kernel<T, 2><<<slices, kWave, 0, st>>>(nx, m, coefp(l), rbuf(l), zbuf(l), sh, back);
+        else if (DIM == 2 && nx <= 4 * kWave)
+          mg_sweep_columns_kernel<T, 4><<<slices, kWave, 0, st>>>(nx, m, coefp(l), rbuf(l), zbuf(l), sh, back);
+        else if (back)
+          mg_sweep_lex_kernel<T, DIM, true><<<slices, 256, 0, st>>>(nx, m, coefp(l), rbuf(l), zbuf(l), sh);
+        else
+          mg_sweep_lex_kernel<T, DIM, false><<<slices, 256, 0, st>>>(nx, m, coefp(l), rbuf(l), zbuf(l), sh);
+      }
     } else if (pair) {
       if (wide(m))
         mg_smooth_pair_kernel<T, DIM, kMgSB><<<grid_pair(nx, m), 256, 0, st>>>(nx, m, slices, coefp(l), rbuf(l), zbuf(l), sh);
@@ -548,7 +860,7 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
       mg_smooth_kernel<T, DIM, 1><<<gridb, 256, 0, st>>>(nx, m, slices, coefp(l), rbuf(l), zbuf(l), sh);
     }
     tend(tb.timer);
-    if (l + 1 < NL) {
+    {
       const int nxc = tb.mg[l + 1].nx;
       const int mc = (int)tb.mg[l + 1].m;
       dim3 gc((mc + 255) / 256, slices);
@@ -577,7 +889,21 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
       tend(tb.timer);
     }
   }
-  for (int l = NL - 2; l >= 0; --l) {
+  {
+    MgTail<T> lv{NL - lt, {}, {}};
+    for (int l = lt; l < NL; ++l) {
+      lv.nx[l - lt] = tb.mg[l].nx;
+      lv.coef[l - lt] = coefp(l);
+    }
+    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&mg_tail_kernel<T, DIM>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    (void)lds_ok;
+    tbeg(tb.timer, KF_MG_SMOOTH, 2.0 * cs * tb.mg[lt].m);
+    mg_tail_kernel<T, DIM><<<slices, kTailThreads, tail_lds, st>>>(lv, rbuf(lt), lt == 0 ? spec : zbuf(lt), sh,
+                                                                   tb.mg_smoother);
+    tend(tb.timer);
+  }
+  for (int l = lt - 1; l >= 0; --l) {
     const int nx = tb.mg[l].nx;
     const int m = (int)tb.mg[l].m;
     const int nxc = tb.mg[l + 1].nx;
@@ -590,12 +916,6 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
     else
       mg_prolong_kernel<T, DIM, 1><<<gridb, 256, 0, st>>>(nx, m, nxc, mc, slices, zbuf(l), zbuf(l + 1), out, sh);
     tend(tb.timer);
-  }
-  if (NL == 1) {
-    // single-point grid: the smoothed value is the exact solve; copy it back
-    const int m = (int)tb.mg[0].m;
-    dim3 grid1((m + 255) / 256, slices);
-    mg_prolong_kernel<T, DIM, 1><<<grid1, 256, 0, st>>>(1, m, 0, 0, slices, zbuf(0), zbuf(0), spec, sh);
   }
 }
 
