@@ -51,7 +51,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 PRECOND_FAMILIES = ("time_fwd", "dst_rows", "dst_ax2", "dst_last_solve", "time_inv", "mg_smooth",
-                    "mg_restrict", "mg_prolong")
+                    "mg_restrict", "mg_prolong", "modes")
 
 
 # kernel sources behind each timed family (to tell whether recorded counters
@@ -59,12 +59,13 @@ PRECOND_FAMILIES = ("time_fwd", "dst_rows", "dst_ax2", "dst_last_solve", "time_i
 _TIME_SOURCES = ["precond.hip", "time_common.hpp", "time_sk.hip", "time_ip.hpp", "time_ip_fwd_f64.hip",
                  "time_ip_inv_f64.hip", "time_ip_fwd_f32.hip", "time_ip_inv_f32.hip", "time_bl.hip", "time_cz.hip",
                  "time_pr.hip", "fft_lds.hpp", "fft_reg.hpp"]
+_DST_SOURCES = ["dst.hip", "modes.hip", "dst_line.hpp", "fft_lds.hpp"]
 FAMILY_SOURCES = {
     "gs_update": ["krylov.hip"], "mdot": ["krylov.hip"], "combine": ["krylov.hip"],
     "kkt_apply": ["kkt.hip", "stencil.hpp", "fem.hip", "fem.hpp"], "time_fwd": _TIME_SOURCES, "time_inv": _TIME_SOURCES,
-    "dst_rows": ["dst.hip", "fft_lds.hpp"], "dst_last_solve": ["dst.hip", "fft_lds.hpp"],
-    "dst_ax2": ["dst.hip", "fft_lds.hpp"], "mg_smooth": ["multigrid.hip"], "mg_restrict": ["multigrid.hip"],
-    "mg_prolong": ["multigrid.hip"], "ideal_step": ["ideal.hip"],
+    "dst_rows": _DST_SOURCES, "dst_last_solve": _DST_SOURCES,
+    "dst_ax2": _DST_SOURCES, "mg_smooth": ["multigrid.hip"], "mg_restrict": ["multigrid.hip"],
+    "mg_prolong": ["multigrid.hip"], "ideal_step": ["ideal.hip"], "modes": ["modes.hip"],
 }
 
 

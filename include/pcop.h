@@ -124,7 +124,9 @@ typedef struct {
  *              coefficients of the new vector against the basis exceed
  *              reorth_tol times its norm (0 = always, < 0 = never).
  *   time_cols  kernels of the two time passes (steps 1 and 3-4 of P_eps^{-1}):
- *              0 automatic; -1 Stockham with two LDS buffers and as many
+ *              0 automatic (with PCOP_DST in FP64, nx >= 7 and dst_kernel = 0
+ *              too: no time pass, both systems of P_eps solved exactly by
+ *              recurrences along time in the sine modes); -1 Stockham with two LDS buffers and as many
  *              spatial points per block as fit; -4 / -8 / -16 two buffers
  *              with at most that many points per block; 4 / 8 / 16 in-place
  *              Stockham (one LDS buffer) with at most that many points per
@@ -146,7 +148,8 @@ typedef struct {
  *              points; n = 127 by a Rader transform, 16 / 32 points); for
  *              other n, 64 / -64 are read as 16 / -16 (Stockham) or fall
  *              back to the automatic choice (chirp-z).
- *   dst_kernel sine-transform kernels of step 2 (PCOP_DST): 0 automatic,
+ *   dst_kernel sine-transform kernels of step 2 (PCOP_DST): 0 automatic
+ *              (FP64: 4, FP32: 1; by modes the transforms' own passes),
  *              1 register-resident lines, 2 lines staged through LDS,
  *              3 register-resident lines with twice as many strided lines
  *              per block (512 threads), 4 strided lines through a
@@ -255,7 +258,9 @@ pcop_status pcop_rhs(pcop_ctx ctx, const double* g, const double* f, const doubl
 pcop_status pcop_kkt_apply(pcop_ctx ctx, const double* x, double* y, int transpose);
 
 /* w = P_eps^{-1} v by the four steps of Section 2.1 (time FFT with the D_eps
- * scaling, shifted spatial solves, inverse FFT, [[I,-I],[I,I]] combination).
+ * scaling, shifted spatial solves, inverse FFT, [[I,-I],[I,I]] combination),
+ * or, with sine transforms in FP64 and automatic kernels, by modes (see
+ * time_cols): the same vector up to rounding.
  * v, w: device vectors; they may alias. */
 pcop_status pcop_precond_apply(pcop_ctx ctx, const double* v, double* w);
 
@@ -337,7 +342,9 @@ pcop_status pcop_error_eh(pcop_ctx ctx, const double* x, const double* yN, const
 /* Host copy of a few derived scalars: tau, alpha[batch], eps. */
 pcop_status pcop_get_params(pcop_ctx ctx, double* tau, double* alpha, double* eps);
 
-/* Kernel choices in effect (after tuning):
+/* Kernel choices in effect (after tuning; where the preconditioner runs by
+ * modes, time_cols and dst_kernel name what the time passes and the other
+ * solves with sine transforms would take):
  *   time_cols      Stockham: -P (two LDS buffers, P points per block) or
  *                  +P (in place); chirp-z (nt - 1 with a prime factor above
  *                  17, or no Stockham tile fits LDS): +P (P points, 256

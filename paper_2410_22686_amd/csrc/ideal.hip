@@ -7,19 +7,12 @@
 // real, so step s carries both recurrences in one complex slice per member:
 //   c = (v_2^s + z_2^{s-1}) + i (v_1^{n-1-s} + z_1^{n-s}),  T_0 c' = c,
 //   z_2^s = Re c', z_1^{n-1-s} = Im c'.
-// With multigrid each step is one V-cycle, an approximate solve, so the n
-// steps are n dependent launch sequences.  With sine transforms every T_0 is
-// diagonal in the same modes: the slices of all steps are transformed at once,
-// each mode runs its own scalar recurrence along time,
-//   c'^s = (c^s + c'^{s-1}) / ((1 + alpha) + tau mu),
-// and all slices are transformed back (2-D nx = 127, n = 127: 508 dependent
-// launches of one slice each, 2200 us per apply, became eight over the whole
-// vector).
-// Storage inside the spectrum buffer: sequential, z[b][2][n][m] (type T)
-// followed by the slice buffer c[b][m] (complex T); by modes, c[b][n][m]
-// (complex T, the same size as z).
-#include <algorithm>
-
+// The n steps are dependent launch sequences of one slice each, needed where a
+// step is one V-cycle, no exact solve (and on the 3 x 3 grid); with sine
+// transforms the steps run by modes instead (modes.hip, eps = 0; 2-D nx = 127,
+// n = 127: 508 launches, 2200 us per apply, before).
+// Storage inside the spectrum buffer: z[b][2][n][m] (type T) followed by the
+// slice buffer c[b][m] (complex T).
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -78,137 +71,9 @@ __global__ void __launch_bounds__(256) ideal_combine_kernel(Geo g, const T* __re
   }
 }
 
-// c^s = scale (v_2^s + i v_1^{n-1-s}) for every step s
 template <class T>
-__global__ void __launch_bounds__(256) ideal_pack_kernel(Geo g, const double* __restrict__ v, cx<T>* __restrict__ c,
-                                                         const double* __restrict__ vscale, int vs_stride,
-                                                         const int* __restrict__ active) {
-  const int b = blockIdx.z;
-  if (active && !active[b]) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.m) return;
-  const int n = g.n, m = g.m;
-  const double sc = vscale ? vscale[(size_t)b * vs_stride] : 1.0;
-  const double* v1 = v + (size_t)b * g.vs;
-  const double* v2 = v1 + (size_t)n * m;
-  for (int s = blockIdx.y; s < n; s += gridDim.y)
-    c[((size_t)b * n + s) * m + i] =
-        cx<T>{(T)(sc * v2[(size_t)s * m + i]), (T)(sc * v1[(size_t)(n - 1 - s) * m + i])};
-}
-
-// The recurrences, in place (FP64 state).  A block owns kModes neighbouring
-// modes (whole lines of the rows it touches) and splits their steps into CH
-// chunks: each thread runs its chunk from zero to get the value it passes on,
-// the carries are chained through LDS, and a second run from its carry writes
-// the result.  CH = 1 where the modes alone fill the chip (one read less),
-// else 16, so that a short mode list is not a serial walk through memory.
-constexpr int kModes = 16;
-constexpr int kModeAhead = 8;  // loads in flight per thread
-template <class T, int CH>
-__global__ void __launch_bounds__(256) ideal_modes_kernel(Geo g, cx<T>* __restrict__ c, const double* __restrict__ mu1,
-                                                          const double* __restrict__ alpha, double cnorm,
-                                                          const int* __restrict__ active) {
-  constexpr int NM = 256 / CH;  // modes per block
-  __shared__ cx<double> ends[CH][NM];
-  const int b = blockIdx.y;
-  if (active && !active[b]) return;
-  const int i = blockIdx.x * NM + threadIdx.x % NM, q = threadIdx.x / NM;
-  const int n = g.n, m = g.m, nx = g.nx;
-  const bool in = i < m;
-  const int im = in ? i : m - 1;
-  double mu = mu1[im % nx] + mu1[(im / nx) % nx];
-  if (g.dim == 3) mu += mu1[im / (nx * nx)];
-  const double rd = 1.0 / ((1.0 + alpha[b]) + g.tau * mu);
-  const int len = (n + CH - 1) / CH;
-  const int s0 = min(n, q * len), s1 = min(n, s0 + len);
-  cx<T>* cb = c + (size_t)b * n * m + im;
-  auto walk = [&](cx<double> z, auto&& put) {
-    for (int s = s0; s < s1; s += kModeAhead) {
-      cx<T> y[kModeAhead];
-#pragma unroll
-      for (int u = 0; u < kModeAhead; ++u) y[u] = cb[(size_t)min(s + u, n - 1) * m];
-#pragma unroll
-      for (int u = 0; u < kModeAhead; ++u)
-        if (s + u < s1) {
-          z.x = (cnorm * (double)y[u].x + z.x) * rd;
-          z.y = (cnorm * (double)y[u].y + z.y) * rd;
-          put(s + u, z);
-        }
-    }
-    return z;
-  };
-  cx<double> z{0.0, 0.0};
-  if constexpr (CH > 1) {
-    ends[q][threadIdx.x % NM] = walk(z, [](int, cx<double>) {});
-    double decay = 1.0;  // rd^len, the weight of a carry one chunk on
-    for (int u = 0; u < len; ++u) decay *= rd;
-    __syncthreads();
-    for (int p = 0; p < q; ++p) {
-      const cx<double> e = ends[p][threadIdx.x % NM];
-      z = cx<double>{e.x + decay * z.x, e.y + decay * z.y};
-    }
-  }
-  // a lane past the last mode repeats it without storing
-  walk(z, [&](int s, cx<double> v) {
-    if (in) cb[(size_t)s * m] = cx<T>{(T)v.x, (T)v.y};
-  });
-}
-
-// w_1^j = z_1^j - z_2^j, w_2^j = z_1^j + z_2^j with z_2^s = Re c^s,
-// z_1^{n-1-s} = Im c^s (added to w when accum)
-template <class T>
-__global__ void __launch_bounds__(256) ideal_unpack_kernel(Geo g, const cx<T>* __restrict__ c, double* __restrict__ w,
-                                                           int accum, const int* __restrict__ active) {
-  const int b = blockIdx.z;
-  if (active && !active[b]) return;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= g.m) return;
-  const int n = g.n, m = g.m;
-  const cx<T>* cb = c + (size_t)b * n * m + i;
-  double* w1 = w + (size_t)b * g.vs + i;
-  double* w2 = w1 + (size_t)n * m;
-  for (int j = blockIdx.y; j < n; j += gridDim.y) {
-    const double a = (double)cb[(size_t)(n - 1 - j) * m].y, d = (double)cb[(size_t)j * m].x;
-    const size_t o = (size_t)j * m;
-    if (accum) {
-      w1[o] += a - d;
-      w2[o] += a + d;
-    } else {
-      w1[o] = a - d;
-      w2[o] = a + d;
-    }
-  }
-}
-
-template <class T>
-static bool ideal_by_modes(const Geo& g, const double* v, double* w, void* spec, const PrecondTables& tb,
-                           const double* vscale, int vs_stride, int accum, hipStream_t st) {
-  cx<T>* c = reinterpret_cast<cx<T>*>(spec);
-  const bool fp32 = sizeof(T) == 4;
-  const double nm = (double)g.n * g.m * tb.nact;
-  const dim3 gp((g.m + 255) / 256, std::min(g.n, 65535), g.B);
-  tbeg(tb.timer, KF_IDEAL_STEP, (16.0 + sizeof(cx<T>)) * nm);
-  ideal_pack_kernel<T><<<gp, 256, 0, st>>>(g, v, c, vscale, vs_stride, tb.active);
-  tend(tb.timer);
-  if (!launch_dst_transform(g, c, fp32, tb, (long long)g.B * g.n, st)) return false;
-  tbeg(tb.timer, KF_IDEAL_STEP, 2.0 * sizeof(cx<T>) * nm);
-  // 256 waves' worth of modes per member and more need no split in time
-  if ((long long)g.m * g.B >= 65536)
-    ideal_modes_kernel<T, 1><<<dim3((g.m + 255) / 256, g.B), 256, 0, st>>>(g, c, tb.mu1, tb.alpha, dst_norm(g), tb.active);
-  else
-    ideal_modes_kernel<T, 16><<<dim3((g.m + kModes - 1) / kModes, g.B), 256, 0, st>>>(g, c, tb.mu1, tb.alpha,
-                                                                                     dst_norm(g), tb.active);
-  tend(tb.timer);
-  if (!launch_dst_transform(g, c, fp32, tb, (long long)g.B * g.n, st)) return false;
-  tbeg(tb.timer, KF_COMBINE, (sizeof(cx<T>) + (accum ? 32.0 : 16.0)) * nm);
-  ideal_unpack_kernel<T><<<gp, 256, 0, st>>>(g, c, w, accum, tb.active);
-  tend(tb.timer);
-  return true;
-}
-
-template <class T>
-static bool ideal_by_steps(const Geo& g, const double* v, double* w, void* spec, const PrecondTables& tb,
-                              const double* unit, const double* vscale, int vs_stride, int accum, hipStream_t st) {
+static bool ideal_by_steps(const Geo& g, const double* v, double* w, void* spec, int spatial, const PrecondTables& tb,
+                           const double* unit, const double* vscale, int vs_stride, int accum, hipStream_t st) {
   T* z = reinterpret_cast<T*>(spec);
   const size_t zbytes = sizeof(T) * (size_t)g.B * 2 * g.n * g.m;
   cx<T>* c = reinterpret_cast<cx<T>*>(reinterpret_cast<char*>(spec) + ((zbytes + 255) & ~(size_t)255));
@@ -221,7 +86,9 @@ static bool ideal_by_steps(const Geo& g, const double* v, double* w, void* spec,
     tend(tb.timer);
     if (s == g.n) break;
     // one slice per member, shift lam_0 + alpha_b with lam_0 = 1: T_0 = (1 + alpha) I + tau K
-    if (!launch_mg_solve(g, c, fp32, tb, 1, unit, st)) return false;
+    const bool ok = (spatial == 0) ? launch_dst_solve(g, c, fp32, tb, 1, unit, st)
+                                   : launch_mg_solve(g, c, fp32, tb, 1, unit, st);
+    if (!ok) return false;
   }
   const long long nm = (long long)g.n * g.m;
   dim3 gc((unsigned)((nm + 255) / 256), g.B);
@@ -240,12 +107,9 @@ size_t ideal_spec_bytes(const Geo& g, bool fp32) {
 bool launch_ideal_precond(const Geo& g, const double* v, double* w, void* spec, bool fp32, int spatial,
                           const PrecondTables& tb, const double* unit, const double* vscale, int vs_stride,
                           int accum, hipStream_t st) {
-  if (spatial == 0) {
-    if (fp32) return ideal_by_modes<float>(g, v, w, spec, tb, vscale, vs_stride, accum, st);
-    return ideal_by_modes<double>(g, v, w, spec, tb, vscale, vs_stride, accum, st);
-  }
-  if (fp32) return ideal_by_steps<float>(g, v, w, spec, tb, unit, vscale, vs_stride, accum, st);
-  return ideal_by_steps<double>(g, v, w, spec, tb, unit, vscale, vs_stride, accum, st);
+  if (tb.by_modes) return launch_modes_precond(g, v, w, spec, tb.mode_ends, fp32, tb, 0.0, vscale, vs_stride, accum, st);
+  if (fp32) return ideal_by_steps<float>(g, v, w, spec, spatial, tb, unit, vscale, vs_stride, accum, st);
+  return ideal_by_steps<double>(g, v, w, spec, spatial, tb, unit, vscale, vs_stride, accum, st);
 }
 
 }  // namespace pcop

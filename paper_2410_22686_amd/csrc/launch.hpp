@@ -25,7 +25,7 @@ inline int resident_blocks(K kernel, int threads, size_t dyn_lds) {
 // family and its algorithmic HBM bytes.
 enum KFamily {
   KF_KKT = 0, KF_TIME_FWD, KF_DST_ROWS, KF_DST_AX2, KF_DST_LAST, KF_TIME_INV, KF_MG_SMOOTH,
-  KF_MG_RESTRICT, KF_MG_PROLONG, KF_MDOT, KF_UPDATE, KF_COMBINE, KF_SMALL, KF_IDEAL_STEP, KF_COUNT
+  KF_MG_RESTRICT, KF_MG_PROLONG, KF_MDOT, KF_UPDATE, KF_COMBINE, KF_SMALL, KF_IDEAL_STEP, KF_MODES, KF_COUNT
 };
 struct KTimer {
   void (*begin)(void* self, int family, double bytes);
@@ -80,6 +80,9 @@ struct PrecondTables {
   int ncu;               // compute units of the device (persistent grids)
   int dst_variant;       // 0: register kernels, 1: LDS-staged kernels, 2: register, 8-line column tiles
   int time_cols;         // time-kernel request, as pcop_options::time_cols
+  bool by_modes;         // sine transforms: the preconditioner by modes (modes.hip)
+  double eps;            // epsilon of C_{eps,n}
+  void* mode_ends;       // its chunk ends (mode_ends_bytes)
   const KTimer* timer;   // or null
   FftPlan plan;          // radices of n
   int mg_levels;
@@ -129,11 +132,19 @@ bool launch_mg_solve(const Geo& g, void* spec, bool fp32, const PrecondTables& t
                      hipStream_t st);
 bool launch_dst_solve(const Geo& g, void* spec, bool fp32, const PrecondTables& tb, int spm, const double* lam,
                       hipStream_t st);
-// the sine transform over every axis of nslices consecutive complex slices, in
-// place; a second one times dst_norm(g) inverts it
-bool launch_dst_transform(const Geo& g, void* data, bool fp32, const PrecondTables& tb, long long nslices,
-                          hipStream_t st);
+// the sine transform along one axis of nslices consecutive complex slices, in
+// place; over every axis twice, times dst_norm(g), it is the identity
+bool launch_dst_axis(const Geo& g, void* data, bool fp32, const PrecondTables& tb, long long nslices, int axis,
+                     hipStream_t st);
 double dst_norm(const Geo& g);
+// w = P_eps^{-1} v (eps = 0: P^{-1}) with sine transforms by modes (modes.hip):
+// c holds [B][n][m] complex, ends mode_ends_bytes(g, fp32) bytes
+constexpr int kModeChunks = 16;
+bool modes_exist(const Geo& g);
+size_t mode_ends_bytes(const Geo& g, bool fp32);
+bool launch_modes_precond(const Geo& g, const double* v, double* w, void* c, void* ends, bool fp32,
+                          const PrecondTables& tb, double eps, const double* vscale, int vs_stride, int accum,
+                          hipStream_t st);
 // ideal RBD preconditioner; unit = device (1.0, 0.0);
 // uses ideal_spec_bytes(g, fp32) bytes of spec
 bool launch_ideal_precond(const Geo& g, const double* v, double* w, void* spec, bool fp32, int spatial,

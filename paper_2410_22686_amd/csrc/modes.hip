@@ -1,0 +1,568 @@
+// The RBD preconditioners with sine transforms, by modes.  With a = 1 every
+// spatial operator is diagonal in the sine modes, so both block systems of
+// P_eps (eq. matrix_P_eps; P of eq. matrix_P is eps = 0) fall apart into one
+// scalar system per mode and block,
+//   d z^j - z^{j-1} = y^j (block 2; block 1 the same backward in time),
+//   z^0 before the first level = eps z^n,   d = 1 + alpha + tau mu > 1
+// (Q1 elements: mu = sum k/m, the right-hand side over the mass eigenvalue),
+// a recurrence along time closed by
+//   z^n = S / (1 - eps D),  S its value from a zero start, D = d^{-n}.
+// No time transform, and so no scaling with eps^{j/n}: the same solution as the
+// four steps of Section 2.1 (error against 64-bit references 1e-15 in both),
+// for any number of levels at the same cost.
+//
+// Both blocks ride in one complex slice per step, c^s = v_2^s + i v_1^{n-1-s}
+// (z_2^s = Re, z_1^{n-1-s} = Im), so that both recurrences run forward in s:
+//   rows in    read v, transform along x1, write c          (mode_rows_in)
+//   [x2 in 3-D]
+//   last axis  transform, recurrence, transform back
+//   [x2 in 3-D]
+//   rows out   transform along x1, combine w_1 = z_1 - z_2,
+//              w_2 = z_1 + z_2                               (mode_rows_out)
+// The recurrence couples all steps of a mode, the transform all modes of a
+// line.  Where the lines of one step fill the chip, blocks march along a chunk
+// of steps with the state of their modes in registers: transform, accumulate
+// and write (mode_march_in), chain the chunks (mode_chain), recurrence and
+// transform back (mode_march_out); two passes of the vector in all.  Smaller
+// shapes take whole passes for the transforms and one for the recurrences
+// (mode_scan), which split in time inside a block.
+#include <algorithm>
+
+#include "common.hpp"
+#include "dst_line.hpp"
+#include "launch.hpp"
+
+namespace pcop {
+
+// what a mode's recurrence needs
+struct ModeParams {
+  const double* mu1;    // [nx] 1-D eigenvalues (k/m with Q1 elements)
+  const double* im1;    // [nx] 1/m, or null
+  const double* alpha;  // [B]
+  const int* active;    // [B] or null
+  double eps;           // 0: the ideal preconditioner
+  double cnorm;         // dst_norm, applied by rows in
+};
+
+__device__ __forceinline__ double mode_mu(const Geo& g, const double* mu1, int i) {
+  double mu = mu1[i % g.nx] + mu1[(i / g.nx) % g.nx];
+  if (g.dim == 3) mu += mu1[i / (g.nx * g.nx)];
+  return mu;
+}
+
+// x^n for n >= 0
+__device__ __forceinline__ double ipow(double x, int n) {
+  double r = 1.0;
+  for (; n > 0; n >>= 1, x *= x)
+    if (n & 1) r *= x;
+  return r;
+}
+
+// ---------------------------------------------------------------------------
+// contiguous lines, register-resident (as dst_reg_kernel): TL = L/8 threads
+// per line.  The odd extension's second half goes through LDS (loaded twice
+// from memory the pass in took 1.30 instead of 1.14 ms, the pass out 1.03
+// instead of 0.94, 2-D nx = 511, n = 511).  HBM-bound: 3.8 and 4.6 TB/s.
+// ---------------------------------------------------------------------------
+// the odd extension's second half, positions t + TL k for k = 4..7, from the
+// first (position p mirrors L - p; positions 0 and N + 1 hold zero)
+template <class T, int L, int TL>
+__device__ __forceinline__ void mirror(cx<T> (&z)[8], int t, cx<T>* lbuf) {
+  line_sync<TL>();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) lbuf[pidx<T>(t + TL * k)] = z[k];
+  line_sync<TL>();
+#pragma unroll
+  for (int k = 4; k < 8; ++k) {
+    const int pos = t + TL * k;
+    const cx<T> q = lbuf[pidx<T>(pos == L / 2 ? 0 : L - pos)];
+    z[k] = cx<T>{-q.x, -q.y};
+  }
+}
+
+template <class T, int L>
+__global__ void __launch_bounds__(reg_threads(L)) mode_rows_in_kernel(Geo g, const double* __restrict__ v,
+                                                                      cx<T>* __restrict__ c,
+                                                                      const cx<T>* __restrict__ twL,
+                                                                      const double* __restrict__ vscale, int vs_stride,
+                                                                      ModeParams mp) {
+  constexpr int N = L / 2 - 1, TL = L / 8, NT = reg_threads(L), LPB = NT / TL, LD = line_ld(L);
+  __shared__ cx<T> buf[LPB * LD];
+  const int lid = threadIdx.x / TL, t = threadIdx.x - lid * TL;
+  const int inner = g.m / N;  // lines per slice
+  // 32 bits hold the number of lines (2^32 of 7 points would be 480 GB)
+  const unsigned total = (unsigned)g.B * g.n * inner;
+  const unsigned ln = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * LPB + lid;
+  const unsigned sl = min(ln, total - 1) / inner;
+  const int li = (int)(min(ln, total - 1) - sl * inner);
+  const int b = (int)(sl / g.n), s = (int)(sl - (unsigned)b * g.n);
+  const bool valid = ln < total && !(mp.active && !mp.active[b]);
+  if (__syncthreads_or(valid) == 0) return;
+  const double sc = mp.cnorm * (vscale ? vscale[(size_t)b * vs_stride] : 1.0);
+  const double* v1 = v + (size_t)b * g.vs + (size_t)(g.n - 1 - s) * g.m + (size_t)li * N;
+  const double* v2 = v + (size_t)b * g.vs + (size_t)(g.n + s) * g.m + (size_t)li * N;
+  cx<T> z[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int pos = t + TL * k;
+    z[k] = valid && pos != 0 ? cx<T>{(T)(sc * v2[pos - 1]), (T)(sc * v1[pos - 1])} : cx<T>{0, 0};
+  }
+  mirror<T, L, TL>(z, t, buf + lid * LD);
+  RegStages<T, L, TL, -1, 1>::run(z, t, buf + lid * LD, twL);
+  if (!valid) return;
+  cx<T>* out = c + (size_t)sl * g.m + (size_t)li * N;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int pos = t + TL * k;
+    if (pos >= 1) out[pos - 1] = z[k];
+  }
+}
+
+// threads per block of rows out: the two lines of a pair at least
+constexpr int rows_out_threads(int L) { return reg_threads(L) > 2 * (L / 8) ? reg_threads(L) : 2 * (L / 8); }
+
+// A block's lines come in pairs, the same line of slices s and n - 1 - s: the
+// pair exchanges its transforms through LDS and writes both levels of w.
+template <class T, int L, bool ACCUM>
+__global__ void __launch_bounds__(rows_out_threads(L)) mode_rows_out_kernel(Geo g, const cx<T>* __restrict__ c,
+                                                                            double* __restrict__ w,
+                                                                            const cx<T>* __restrict__ twL,
+                                                                            ModeParams mp) {
+  constexpr int N = L / 2 - 1, TL = L / 8, NT = rows_out_threads(L), LPB = NT / TL, LD = line_ld(L);
+  __shared__ cx<T> buf[LPB * LD];
+  const int lid = threadIdx.x / TL, t = threadIdx.x - lid * TL;
+  const int inner = g.m / N, npair = (g.n + 1) / 2;
+  const unsigned total = (unsigned)g.B * npair * inner;
+  const unsigned pl = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * (LPB / 2) + lid / 2;
+  const unsigned pr = min(pl, total - 1) / inner;
+  const int li = (int)(min(pl, total - 1) - pr * inner);
+  const int b = (int)(pr / npair), p = (int)(pr - (unsigned)b * npair);
+  const bool valid = pl < total && !(mp.active && !mp.active[b]);
+  if (__syncthreads_or(valid) == 0) return;
+  const int s = (lid & 1) ? g.n - 1 - p : p;
+  const cx<T>* in = c + ((size_t)b * g.n + s) * g.m + (size_t)li * N;
+  cx<T>* lbuf = buf + lid * LD;
+  cx<T> z[8];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int pos = t + TL * k;
+    z[k] = valid && pos != 0 ? in[pos - 1] : cx<T>{0, 0};
+  }
+  mirror<T, L, TL>(z, t, lbuf);
+  RegStages<T, L, TL, -1, 1>::run(z, t, lbuf, twL);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) lbuf[pidx<T>(t + TL * k)] = z[k];
+  __syncthreads();
+  // the middle slice of an odd number is its own partner, written once
+  if (!valid || ((lid & 1) && s == p)) return;
+  const cx<T>* other = buf + (lid ^ 1) * LD;
+  double* w1 = w + (size_t)b * g.vs + (size_t)s * g.m + (size_t)li * N;
+  double* w2 = w1 + (size_t)g.n * g.m;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int pos = t + TL * k;
+    if (pos >= 1) {
+      const double z1 = (double)other[pidx<T>(pos)].y, z2 = (double)z[k].x;
+      if (ACCUM) {
+        w1[pos - 1] += z1 - z2;
+        w2[pos - 1] += z1 + z2;
+      } else {
+        w1[pos - 1] = z1 - z2;
+        w2[pos - 1] = z1 + z2;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The recurrences of all modes, in place (FP64 state).  A block owns 256 / CH
+// neighbouring modes and splits their steps into CH chunks: each thread runs
+// its chunk from zero to get the value it passes on, the values are chained
+// through LDS and closed with eps, and a second run from its carry writes the
+// result (the second read comes from the caches on the shapes that take this
+// kernel).  CH = 1 where the modes alone fill the chip, else 16, so that a
+// short mode list is not a serial walk through memory.
+// ---------------------------------------------------------------------------
+constexpr int kScanAhead = 8;  // loads in flight per thread
+template <class T, int CH>
+__global__ void __launch_bounds__(256) mode_scan_kernel(Geo g, cx<T>* __restrict__ c, ModeParams mp) {
+  constexpr int NM = 256 / CH;  // modes per block
+  __shared__ cx<double> ends[CH][NM];
+  const int b = blockIdx.y;
+  if (mp.active && !mp.active[b]) return;
+  const int k = threadIdx.x % NM, q = threadIdx.x / NM;
+  const int i = blockIdx.x * NM + k;
+  const int n = g.n, m = g.m, nx = g.nx;
+  const bool in = i < m;
+  const int im = in ? i : m - 1;
+  const double rd = 1.0 / ((1.0 + mp.alpha[b]) + g.tau * mode_mu(g, mp.mu1, im));
+  double f = 1.0;
+  if (mp.im1) {
+    f = mp.im1[im % nx] * mp.im1[(im / nx) % nx];
+    if (g.dim == 3) f *= mp.im1[im / (nx * nx)];
+  }
+  const int len = (n + CH - 1) / CH;
+  const int s0 = min(n, q * len), s1 = min(n, s0 + len);
+  cx<T>* cb = c + (size_t)b * n * m + im;
+  auto walk = [&](cx<double> z, auto&& put) {
+    for (int s = s0; s < s1; s += kScanAhead) {
+      cx<T> y[kScanAhead];
+#pragma unroll
+      for (int u = 0; u < kScanAhead; ++u) y[u] = cb[(size_t)min(s + u, n - 1) * m];
+#pragma unroll
+      for (int u = 0; u < kScanAhead; ++u)
+        if (s + u < s1) {
+          z.x = (f * (double)y[u].x + z.x) * rd;
+          z.y = (f * (double)y[u].y + z.y) * rd;
+          put(s + u, z);
+        }
+    }
+    return z;
+  };
+  cx<double> z{0.0, 0.0};
+  if (CH > 1 || mp.eps != 0.0) {
+    ends[q][k] = walk(z, [](int, cx<double>) {});
+    __syncthreads();
+    // chunk p passes on ends + rd^{its length} times what it got
+    const double decay = ipow(rd, len);
+    auto chain = [&](cx<double> a, int upto) {
+      for (int p = 0; p < upto; ++p) {
+        const int lp = max(0, min(n - p * len, len));
+        const double dp = lp == len ? decay : ipow(rd, lp);
+        a = cx<double>{ends[p][k].x + dp * a.x, ends[p][k].y + dp * a.y};
+      }
+      return a;
+    };
+    if (mp.eps != 0.0) {
+      const cx<double> S = chain(z, CH);
+      const double close = mp.eps / (1.0 - mp.eps * ipow(rd, n));
+      z = cx<double>{close * S.x, close * S.y};
+    }
+    z = chain(z, q);
+  }
+  // a lane past the last mode repeats it without storing
+  walk(z, [&](int s, cx<double> a) {
+    if (in) cb[(size_t)s * m] = cx<T>{(T)a.x, (T)a.y};
+  });
+}
+
+// ---------------------------------------------------------------------------
+// Marching passes of the last axis.  HBM-bound with two blocks per CU (about 200
+// registers): 0.98 ms each at 2-D nx = 511, n = 511 (4.4 TB/s), where the
+// strided pass with the division and the two time transforms they replace took
+// 2.0 + 1.2 + 1.2 ms.  A tile is LPB neighbouring lines (M/8
+// threads each, half-length transforms as dst_half_kernel); a block takes one
+// tile through the steps [q len, (q + 1) len) of its member.  Thread t of a
+// line keeps the state of modes 8t .. 8t + 7.
+// ---------------------------------------------------------------------------
+template <class T, int L, int NT>
+struct MarchTile {
+  using H = HalfDst<T, L>;
+  static constexpr int M = H::M, N = H::N, TM = H::TM, LPB = NT / TM;
+  static constexpr bool QUAD = TM >= 4;
+  static constexpr int LD = M >= 128 ? M + 4 : line_ld(M);
+  static constexpr int QS = (N * LPB + NT - 1) / NT;
+  static_assert(LPB * TM == NT, "a tile is a whole number of lines");
+  // the tile's (line, element) pairs a thread loads and stores: line tl,
+  // elements te + TM q (see dst_half_kernel)
+  static __device__ __forceinline__ int tl() { return QUAD ? (threadIdx.x >> 2) % LPB : threadIdx.x % LPB; }
+  static __device__ __forceinline__ int te() {
+    return QUAD ? (threadIdx.x & 3) + 4 * (threadIdx.x / (4 * LPB)) : threadIdx.x / LPB;
+  }
+  static __device__ __forceinline__ void load(const cx<T>* __restrict__ src, int l0, int lines, int stride, cx<T>* buf) {
+    const bool ok = l0 + tl() < lines;
+    const int off = l0 + tl() + te() * stride;
+    cx<T> cur[QS];
+#pragma unroll
+    for (int q = 0; q < QS; ++q) cur[q] = ok && te() + TM * q < N ? src[off + q * TM * stride] : cx<T>{0, 0};
+#pragma unroll
+    for (int q = 0; q < QS; ++q)
+      if (te() + TM * q < N) buf[tl() * LD + pidx<T>(te() + TM * q)] = cur[q];
+  }
+  static __device__ __forceinline__ void store(cx<T>* __restrict__ dst, int l0, int lines, int stride, const cx<T>* buf) {
+    if (l0 + tl() < lines) {
+      const int off = l0 + tl() + te() * stride;
+#pragma unroll
+      for (int q = 0; q < QS; ++q)
+        if (te() + TM * q < N) dst[off + q * TM * stride] = buf[tl() * LD + pidx<T>(te() + TM * q)];
+    }
+  }
+};
+
+// (tile, chunk, member) of this block, neighbouring tiles (which share lines
+// of memory) on one XCD at the same time
+struct MarchBlock {
+  int tile, q, b;
+};
+__device__ __forceinline__ MarchBlock march_block(int tiles, int CH) {
+  const int lg = xcd_remap(blockIdx.x, gridDim.x);
+  return MarchBlock{lg % tiles, lg / tiles % CH, lg / (tiles * CH)};
+}
+
+// reciprocal diagonals of modes 8t .. 8t + 7 of the thread's line, and (Q1)
+// the factor of their right-hand sides
+template <class T, int N, bool FEM>
+__device__ __forceinline__ void mode_factors(const Geo& g, const ModeParams& mp, int b, int line, int t,
+                                             double (&rd)[8], double (&f)[8]) {
+  double ml = mp.mu1[line % g.nx], psl = FEM ? mp.im1[line % g.nx] : 1.0;
+  if (g.dim == 3) {
+    ml += mp.mu1[(line / g.nx) % g.nx];
+    if (FEM) psl *= mp.im1[(line / g.nx) % g.nx];
+  }
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const int e = max(8 * t + r - 1, 0);
+    rd[r] = 1.0 / ((1.0 + mp.alpha[b]) + g.tau * (ml + mp.mu1[min(e, N - 1)]));
+    f[r] = FEM ? psl * mp.im1[min(e, N - 1)] : 1.0;
+  }
+}
+
+template <class T, int L, int NT, bool FEM>
+__global__ void __launch_bounds__(NT) mode_march_in_kernel(Geo g, cx<T>* __restrict__ c, cx<T>* __restrict__ ends,
+                                                           const cx<T>* __restrict__ twL, int tiles, int CH, int len,
+                                                           ModeParams mp) {
+  using M_ = MarchTile<T, L, NT>;
+  using H = HalfDst<T, L>;
+  constexpr int M = M_::M, N = M_::N, TM = M_::TM, LPB = M_::LPB, LD = M_::LD;
+  __shared__ cx<T> buf[LPB * LD];
+  __shared__ cx<T> twm[M];
+  __shared__ T sinl[M];
+  const MarchBlock mb = march_block(tiles, CH);
+  if (mp.active && !mp.active[mb.b]) return;
+  for (int k = threadIdx.x; k < M; k += NT) {
+    twm[k] = twL[2 * k];
+    sinl[k] = -twL[k].y;
+  }
+  const int lines = g.m / N;  // per step; also the stride of a line's elements
+  const int l0 = mb.tile * LPB, lid = threadIdx.x / TM, t = threadIdx.x - lid * TM;
+  const int s0 = mb.q * len, s1 = min(g.n, s0 + len);
+  cx<T>* lbuf = buf + lid * LD;
+  double rd[8], f[8];
+  mode_factors<T, N, FEM>(g, mp, mb.b, min(l0 + lid, lines - 1), t, rd, f);
+  cx<double> z[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) z[r] = cx<double>{0.0, 0.0};
+  auto put = [&](const cx<T> (&o)[8]) {
+    line_sync<TM>();
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (8 * t + r >= 1) lbuf[pidx<T>(8 * t + r - 1)] = o[r];
+    __syncthreads();
+  };
+  __syncthreads();
+  for (int s = s0; s < s1; ++s) {
+    cx<T>* cs = c + ((size_t)mb.b * g.n + s) * g.m;
+    M_::load(cs, l0, lines, lines, buf);
+    __syncthreads();
+    cx<T> v[8], o[8];
+    H::pre(v, t, lbuf, sinl);
+    RegStages<T, M, TM, -1, 1>::run(v, t, lbuf, twm);
+    H::post(v, o, t, lbuf);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      if (FEM) o[r] = cx<T>{(T)(f[r] * (double)o[r].x), (T)(f[r] * (double)o[r].y)};
+      z[r] = cx<double>{((double)o[r].x + z[r].x) * rd[r], ((double)o[r].y + z[r].y) * rd[r]};
+    }
+    put(o);
+    M_::store(cs, l0, lines, lines, buf);
+    __syncthreads();
+  }
+  cx<T> e[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) e[r] = cx<T>{(T)z[r].x, (T)z[r].y};
+  put(e);
+  M_::store(ends + ((size_t)mb.b * CH + mb.q) * g.m, l0, lines, lines, buf);
+}
+
+// The values the chunks start from, over their end values from a zero start
+// (one thread per mode).
+template <class T>
+__global__ void __launch_bounds__(256) mode_chain_kernel(Geo g, cx<T>* __restrict__ ends, int CH, int len, ModeParams mp) {
+  const int b = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= g.m || (mp.active && !mp.active[b])) return;
+  const double rd = 1.0 / ((1.0 + mp.alpha[b]) + g.tau * mode_mu(g, mp.mu1, i));
+  const double decay = ipow(rd, len), last = ipow(rd, g.n - (CH - 1) * len);
+  cx<T>* e = ends + (size_t)b * CH * g.m + i;
+  cx<double> z{0.0, 0.0};
+  if (mp.eps != 0.0) {
+    for (int q = 0; q < CH; ++q) {
+      const double d = q + 1 < CH ? decay : last;
+      const cx<T> a = e[(size_t)q * g.m];
+      z = cx<double>{(double)a.x + d * z.x, (double)a.y + d * z.y};
+    }
+    const double close = mp.eps / (1.0 - mp.eps * ipow(rd, g.n));
+    z = cx<double>{close * z.x, close * z.y};
+  }
+  for (int q = 0; q < CH; ++q) {
+    const cx<T> a = e[(size_t)q * g.m];
+    e[(size_t)q * g.m] = cx<T>{(T)z.x, (T)z.y};
+    z = cx<double>{(double)a.x + decay * z.x, (double)a.y + decay * z.y};
+  }
+}
+
+template <class T, int L, int NT>
+__global__ void __launch_bounds__(NT) mode_march_out_kernel(Geo g, cx<T>* __restrict__ c,
+                                                            const cx<T>* __restrict__ starts,
+                                                            const cx<T>* __restrict__ twL, int tiles, int CH, int len,
+                                                            ModeParams mp) {
+  using M_ = MarchTile<T, L, NT>;
+  using H = HalfDst<T, L>;
+  constexpr int M = M_::M, N = M_::N, TM = M_::TM, LPB = M_::LPB, LD = M_::LD;
+  __shared__ cx<T> buf[LPB * LD];
+  __shared__ cx<T> twm[M];
+  __shared__ T sinl[M];
+  const MarchBlock mb = march_block(tiles, CH);
+  if (mp.active && !mp.active[mb.b]) return;
+  for (int k = threadIdx.x; k < M; k += NT) {
+    twm[k] = twL[2 * k];
+    sinl[k] = -twL[k].y;
+  }
+  const int lines = g.m / N;
+  const int l0 = mb.tile * LPB, lid = threadIdx.x / TM, t = threadIdx.x - lid * TM;
+  const int s0 = mb.q * len, s1 = min(g.n, s0 + len);
+  cx<T>* lbuf = buf + lid * LD;
+  double rd[8], f[8];
+  mode_factors<T, N, false>(g, mp, mb.b, min(l0 + lid, lines - 1), t, rd, f);
+  M_::load(starts + ((size_t)mb.b * CH + mb.q) * g.m, l0, lines, lines, buf);
+  __syncthreads();
+  cx<double> z[8];
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const cx<T> a = lbuf[pidx<T>(max(8 * t + r - 1, 0))];
+    z[r] = cx<double>{(double)a.x, (double)a.y};
+  }
+  __syncthreads();
+  for (int s = s0; s < s1; ++s) {
+    cx<T>* cs = c + ((size_t)mb.b * g.n + s) * g.m;
+    M_::load(cs, l0, lines, lines, buf);
+    __syncthreads();
+    // the recurrence, each value back to its slot
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (8 * t + r >= 1) {
+        cx<T>& y = lbuf[pidx<T>(8 * t + r - 1)];
+        z[r] = cx<double>{((double)y.x + z[r].x) * rd[r], ((double)y.y + z[r].y) * rd[r]};
+        y = cx<T>{(T)z[r].x, (T)z[r].y};
+      }
+    line_sync<TM>();
+    cx<T> v[8], o[8];
+    H::pre(v, t, lbuf, sinl);
+    RegStages<T, M, TM, -1, 1>::run(v, t, lbuf, twm);
+    H::post(v, o, t, lbuf);
+    line_sync<TM>();
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (8 * t + r >= 1) lbuf[pidx<T>(8 * t + r - 1)] = o[r];
+    __syncthreads();
+    M_::store(cs, l0, lines, lines, buf);
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Chunks of the marching passes, 0 where whole passes are taken: enough blocks
+// for two rounds of the chip (1024), chunks of at least 8 steps (a chunk's end
+// and start values are two more slices each).
+static int march_chunks(const Geo& g) {
+  const int M = g.nx + 1, lpb = 256 / (M / 8);
+  const long long tiles = ((long long)g.m / g.nx + lpb - 1) / lpb * g.B;
+  const long long ch = std::max<long long>(1, (1024 + tiles - 1) / tiles);
+  return ch * 8 <= g.n && ch <= kModeChunks ? (int)ch : 0;
+}
+
+bool modes_exist(const Geo& g) { return g.nx >= 7; }
+
+size_t mode_ends_bytes(const Geo& g, bool fp32) {
+  return (fp32 ? 8 : 16) * (size_t)g.B * march_chunks(g) * (size_t)g.m;
+}
+
+template <class T, int L>
+static bool modes_L(const Geo& g, const double* v, double* w, cx<T>* c, cx<T>* ends, const PrecondTables& tb,
+                    double eps, const double* vscale, int vs_stride, int accum, hipStream_t st) {
+  const cx<T>* twL = reinterpret_cast<const cx<T>*>(sizeof(T) == 8 ? (const void*)tb.twL64 : (const void*)tb.twL32);
+  const ModeParams mp{tb.mu1, tb.im1, tb.alpha, tb.active, eps, dst_norm(g)};
+  const bool fp32 = sizeof(T) == 4;
+  const long long nslices = (long long)g.B * g.n;
+  const int inner = g.m / g.nx;
+  const double nm = (double)g.n * g.m * tb.nact;
+  const double pass = 2.0 * sizeof(cx<T>) * nm;
+  {
+    constexpr int LPB = reg_threads(L) / (L / 8);
+    const long long lines = nslices * inner;
+    tbeg(tb.timer, KF_DST_ROWS, (16.0 + sizeof(cx<T>)) * nm);
+    mode_rows_in_kernel<T, L><<<(unsigned)((lines + LPB - 1) / LPB), reg_threads(L), 0, st>>>(g, v, c, twL, vscale,
+                                                                                             vs_stride, mp);
+    tend(tb.timer);
+  }
+  if (g.dim == 3 && !launch_dst_axis(g, c, fp32, tb, nslices, 2, st)) return false;
+  const int CH = march_chunks(g);
+  if (CH > 0) {
+    constexpr int NT = 256, LPB = MarchTile<T, L, NT>::LPB;
+    const int tiles = (inner + LPB - 1) / LPB;
+    const int len = (g.n + CH - 1) / CH, chunks = (g.n + len - 1) / len;
+    const dim3 grid((unsigned)((long long)tiles * chunks * g.B));
+    tbeg(tb.timer, KF_DST_LAST, pass);
+    if (mp.im1)
+      mode_march_in_kernel<T, L, NT, true><<<grid, NT, 0, st>>>(g, c, ends, twL, tiles, chunks, len, mp);
+    else
+      mode_march_in_kernel<T, L, NT, false><<<grid, NT, 0, st>>>(g, c, ends, twL, tiles, chunks, len, mp);
+    tend(tb.timer);
+    tbeg(tb.timer, KF_MODES, 0.0);
+    mode_chain_kernel<T><<<dim3((g.m + 255) / 256, g.B), 256, 0, st>>>(g, ends, chunks, len, mp);
+    tend(tb.timer);
+    tbeg(tb.timer, KF_DST_LAST, pass);
+    mode_march_out_kernel<T, L, NT><<<grid, NT, 0, st>>>(g, c, ends, twL, tiles, chunks, len, mp);
+    tend(tb.timer);
+  } else {
+    if (!launch_dst_axis(g, c, fp32, tb, nslices, g.dim == 3 ? 3 : 2, st)) return false;
+    tbeg(tb.timer, KF_MODES, pass);
+    // 64 waves' worth of modes per XCD and more need no split in time
+    if ((long long)g.m * g.B >= 65536)
+      mode_scan_kernel<T, 1><<<dim3((g.m + 255) / 256, g.B), 256, 0, st>>>(g, c, mp);
+    else
+      mode_scan_kernel<T, 16><<<dim3((g.m + 15) / 16, g.B), 256, 0, st>>>(g, c, mp);
+    tend(tb.timer);
+    if (!launch_dst_axis(g, c, fp32, tb, nslices, g.dim == 3 ? 3 : 2, st)) return false;
+  }
+  if (g.dim == 3 && !launch_dst_axis(g, c, fp32, tb, nslices, 2, st)) return false;
+  {
+    constexpr int NT = rows_out_threads(L), PL = NT / (L / 8) / 2;
+    const long long pairs = (long long)g.B * ((g.n + 1) / 2) * inner;
+    const unsigned grid = (unsigned)((pairs + PL - 1) / PL);
+    tbeg(tb.timer, KF_DST_ROWS, (sizeof(cx<T>) + (accum ? 32.0 : 16.0)) * nm);
+    if (accum) mode_rows_out_kernel<T, L, true><<<grid, NT, 0, st>>>(g, c, w, twL, mp);
+    else mode_rows_out_kernel<T, L, false><<<grid, NT, 0, st>>>(g, c, w, twL, mp);
+    tend(tb.timer);
+  }
+  return true;
+}
+
+template <class T>
+static bool modes_T(const Geo& g, const double* v, double* w, void* c, void* ends, const PrecondTables& tb, double eps,
+                    const double* vscale, int vs_stride, int accum, hipStream_t st) {
+#define PCOP_MODES(LL)                                                                                              \
+  case LL:                                                                                                          \
+    return modes_L<T, LL>(g, v, w, reinterpret_cast<cx<T>*>(c), reinterpret_cast<cx<T>*>(ends), tb, eps, vscale,      \
+                          vs_stride, accum, st)
+  switch (2 * (g.nx + 1)) {
+    PCOP_MODES(16);
+    PCOP_MODES(32);
+    PCOP_MODES(64);
+    PCOP_MODES(128);
+    PCOP_MODES(256);
+    PCOP_MODES(512);
+    PCOP_MODES(1024);
+    default: return false;
+  }
+#undef PCOP_MODES
+}
+
+bool launch_modes_precond(const Geo& g, const double* v, double* w, void* c, void* ends, bool fp32,
+                          const PrecondTables& tb, double eps, const double* vscale, int vs_stride, int accum,
+                          hipStream_t st) {
+  if (fp32) return modes_T<float>(g, v, w, c, ends, tb, eps, vscale, vs_stride, accum, st);
+  return modes_T<double>(g, v, w, c, ends, tb, eps, vscale, vs_stride, accum, st);
+}
+
+}  // namespace pcop

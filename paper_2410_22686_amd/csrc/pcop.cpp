@@ -166,7 +166,8 @@ struct Layout {
   int RC = 0;  // Rader convolution length of a prime-factor plan, or 0
   size_t sc, H, coef, red, partial, wnorm2, norm, skip, active, finish, hcol;
   size_t bcoef, bbeta, bred, bpart, brec;  // block Gram-Schmidt (krylov.hip)
-  size_t basis, zbasis, tmp1, tmp2, xpad, spec;
+  size_t basis, zbasis, tmp1, tmp2, xpad, spec, ends = 0;
+  bool by_modes = false;
   size_t mgcoef[kMaxMgLevels], mgz[kMaxMgLevels], mgr[kMaxMgLevels];
   int mg_levels = 0;
   int mg_nx[kMaxMgLevels];
@@ -255,6 +256,22 @@ void plan_layout(const pcop_problem* p, const pcop_options* o, Layout& L) {
     const size_t ideal = ((t * (size_t)B * 2 * n * m + 255) & ~(size_t)255) + 2 * t * (size_t)B * m;
     L.spec = take(L, std::max<size_t>(csz * (size_t)B * 2 * K * m, o->precond == PCOP_PRECOND_IDEAL ? ideal : 0));
   }
+  {
+    // sine transforms with automatic kernels run by modes: the ideal
+    // preconditioner, and the epsilon-circulant one in FP64 (its FP32 form
+    // keeps the time transforms: the last steps of a mixed solve follow the
+    // FP32 rounding, and with it the operations)
+    Geo g{};
+    g.dim = d;
+    g.nx = nx;
+    g.n = n;
+    g.m = (int)m;
+    g.B = B;
+    const bool automatic = o->time_cols == 0 && o->dst_kernel == 0;
+    L.by_modes = o->spatial == PCOP_DST && modes_exist(g) &&
+                 (o->precond == PCOP_PRECOND_IDEAL || (automatic && !fp32));
+    if (L.by_modes) L.ends = take(L, mode_ends_bytes(g, fp32));
+  }
   L.mg_levels = 0;
   if (o->spatial == PCOP_MG) {
     int lnx = nx;
@@ -282,7 +299,7 @@ void plan_layout(const pcop_problem* p, const pcop_options* o, Layout& L) {
 // ---------------------------------------------------------------------------
 const char* kFamilyName[KF_COUNT] = {"kkt_apply", "time_fwd", "dst_rows", "dst_ax2", "dst_last_solve",
                                      "time_inv", "mg_smooth", "mg_restrict", "mg_prolong", "mdot",
-                                     "gs_update", "combine", "small", "ideal_step"};
+                                     "gs_update", "combine", "small", "ideal_step", "modes"};
 
 struct EventTimer {
   hipStream_t st = nullptr;
@@ -419,6 +436,8 @@ bool run_precond(pcop_ctx c, const Geo& g, const PrecondTables& tb, const double
   if (c->opt.precond == PCOP_PRECOND_IDEAL)
     return launch_ideal_precond(g, v, w, spec, c->fp32, c->opt.spatial, tb, c->at<double>(c->L.unit), vscale,
                                 vs_stride, accum, c->st);
+  if (tb.by_modes)
+    return launch_modes_precond(g, v, w, spec, tb.mode_ends, c->fp32, tb, tb.eps, vscale, vs_stride, accum, c->st);
   return launch_precond(g, v, w, spec, c->fp32, c->opt.spatial, tb, vscale, vs_stride, accum, c->st);
 }
 
@@ -596,7 +615,7 @@ pcop_status tune_kernels(pcop_ctx c) {
     }
   }
   std::vector<int> tcs;
-  if (c->opt.time_cols != 0 || c->opt.precond == PCOP_PRECOND_IDEAL) {
+  if (c->opt.time_cols != 0 || c->tb.by_modes || c->opt.precond == PCOP_PRECOND_IDEAL) {
     tcs.push_back(c->tb.time_cols);
   } else {
     std::vector<int> seen;
@@ -619,7 +638,8 @@ pcop_status tune_kernels(pcop_ctx c) {
     }
   }
   std::vector<int> dvs;
-  if (c->opt.spatial == PCOP_DST && c->opt.dst_kernel == 0) dvs = {0, 1, 2, 3, 4};
+  // (by modes the marching passes, or the choice above, run the lines)
+  if (c->opt.spatial == PCOP_DST && c->opt.dst_kernel == 0 && !c->tb.by_modes) dvs = {0, 1, 2, 3, 4};
   else dvs = {c->tb.dst_variant};
   double* v = c->basis(0);
   double* w = c->basis(1);
@@ -1149,7 +1169,14 @@ pcop_status pcop_setup(pcop_ctx* out, const pcop_problem* prob, const pcop_optio
   tb.pr32 = L.RC > 0 ? c->at<float>(L.pr32) : nullptr;
   tb.time_cols = opts->time_cols;
   tb.mg_smoother = opts->mg_smoother;
-  tb.dst_variant = (opts->dst_kernel >= 2) ? opts->dst_kernel - 1 : 0;
+  // automatic: in FP64 the strided lines through the half-length transform
+  // (2-D nx = 511 2.10 -> 1.41 ms per pass with the division, nx = 255 0.67 ->
+  // 0.47 at three members, nx = 63 31 -> 21 us at four); in FP32 the
+  // register-resident lines
+  tb.dst_variant = opts->dst_kernel >= 2 ? opts->dst_kernel - 1 : opts->dst_kernel == 0 && !c->fp32 ? 3 : 0;
+  tb.by_modes = L.by_modes;
+  tb.eps = c->eps;
+  tb.mode_ends = L.by_modes ? c->at<void>(L.ends) : nullptr;
   c->nb_mdot.fill(opts->krylov_blocks > 0 ? opts->krylov_blocks : L.nblk);
   c->nb_upd = c->nb_mdot;
   c->kkt_jchunk = opts->kkt_jchunk != 0 ? opts->kkt_jchunk : -8;
