@@ -169,9 +169,10 @@ typedef struct {
  *              eq. matrix_P, applied by sequential substitution in time
  *              (n dependent spatial solves with (1 + alpha) I + tau K; the
  *              comparison method of Tables 4 and 8).  time_cols is ignored.
- *   kkt_jchunk KKT matvec kernel: 0 automatic (-8, or the tuner's choice);
+ *   kkt_jchunk KKT matvec kernel: 0 automatic (-8, on small grids fewer
+ *              levels, or the tuner's choice);
  *              1..64 one thread per point marching that many time levels;
- *              -64..-1 LDS-tiled blocks (1024 points and their in-plane
+ *              -64..-1 LDS-tiled blocks (1024 points and their
  *              neighbours staged per level) marching -kkt_jchunk levels
  *              (for nx <= 1024, else as 16).
  *   krylov_blocks  blocks per member of the Krylov reductions: 0 automatic

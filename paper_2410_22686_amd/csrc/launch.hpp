@@ -91,6 +91,8 @@ struct PrecondTables {
   const void* mg_res;    // finest-level residual scratch [B][2K][m] complex
 };
 
+// levels per block of the LDS-tiled matvec where the caller leaves it open
+int kkt_auto_levels(const Geo& g);
 void launch_kkt_apply(const Geo& g, const double* x, double* y, const double* c, const double* alpha,
                       const double* xscale, int xs_stride, const int* active, bool transpose,
                       const double* ecoef, double ediag, double eoff, int jchunk, hipStream_t st,

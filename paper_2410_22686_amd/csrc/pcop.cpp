@@ -694,9 +694,9 @@ pcop_status tune_kernels(pcop_ctx c) {
   }
   // matvec: time levels per thread
   double best_kkt = 1e300;
-  // levels per block of the LDS-tiled kernel (the built-in -8 first), then
+  // levels per block of the LDS-tiled kernel (the built-in choice first), then
   // levels per thread of the one-thread-per-point kernel
-  for (int jc : {-8, -16, -32, 16, 1, 2, 4, 8, 32}) {
+  for (int jc : {c->kkt_jchunk, -8, -16, -32, 16, 1, 2, 4, 8, 32}) {
     if (err != hipSuccess || c->opt.kkt_jchunk != 0) break;
     double ms = 0;
     if (!time_it([&] {
@@ -1179,7 +1179,7 @@ pcop_status pcop_setup(pcop_ctx* out, const pcop_problem* prob, const pcop_optio
   tb.mode_ends = L.by_modes ? c->at<void>(L.ends) : nullptr;
   c->nb_mdot.fill(opts->krylov_blocks > 0 ? opts->krylov_blocks : L.nblk);
   c->nb_upd = c->nb_mdot;
-  c->kkt_jchunk = opts->kkt_jchunk != 0 ? opts->kkt_jchunk : -8;
+  c->kkt_jchunk = opts->kkt_jchunk != 0 ? opts->kkt_jchunk : -kkt_auto_levels(c->g);
   c->pairs_upd.fill(opts->gs_update == 2 ? 1 : 0);
   {
     int dev = 0, ncu = 0;
