@@ -761,17 +761,16 @@ static bool dst_solve(const Geo& g, cx<T>* spec, const PrecondTables& tb, int sp
   return ok;
 }
 
-// the sine transform along one axis (1 = x1, contiguous) of the nslices slices at
+// the sine transform along one strided axis (2 or 3) of the nslices slices at
 // data, in place and unnormalised (dst_norm)
 template <class T>
 static bool dst_axis(const Geo& g, cx<T>* data, const PrecondTables& tb, long long nslices, int axis, hipStream_t st) {
   const DivideParams dp{tb.mu1, nullptr, nullptr, nullptr, 1.0, 1, nullptr};
   const SliceLines sl = slice_lines(g, nslices);
   const bool last = axis == g.dim;
-  tbeg(tb.timer, axis == 1 ? KF_DST_ROWS : last ? KF_DST_LAST : KF_DST_AX2,
+  tbeg(tb.timer, last ? KF_DST_LAST : KF_DST_AX2,
        2.0 * sizeof(cx<T>) * (double)nslices / g.B * tb.nact * g.m);
-  const bool ok = dst_pass<T>(g, data, axis == 1 ? sl.rows : last ? sl.last : sl.ax2, axis == 1, false,
-                              dst_twiddles<T>(tb), dp, tb.dst_variant, tb.ncu, st);
+  const bool ok = dst_pass<T>(g, data, last ? sl.last : sl.ax2, false, false, dst_twiddles<T>(tb), dp, tb.dst_variant, tb.ncu, st);
   tend(tb.timer);
   return ok;
 }

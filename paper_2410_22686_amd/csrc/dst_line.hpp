@@ -119,15 +119,15 @@ constexpr int reg_threads(int L) { return L >= 512 ? (L / 8 > 128 ? L / 8 : 128)
 template <class T, int L>
 struct HalfDst {
   static constexpr int M = L / 2, N = M - 1, TM = M / 8;
-  // y_j (j = t + TM s) from the line's values z_{e+1} at lbuf[pidx(e)]
-  static __device__ __forceinline__ void pre(cx<T> (&v)[8], int t, const cx<T>* lbuf, const T* sinl) {
+  // y_j (j = t + TM s) from the line's values z_{e+1} at lbuf[pidx(e ^ sw)]
+  static __device__ __forceinline__ void pre(cx<T> (&v)[8], int t, const cx<T>* lbuf, const T* sinl, int sw = 0) {
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const int j = t + TM * s;
       if (j == 0) {
         v[s] = cx<T>{0, 0};
       } else {
-        const cx<T> a = lbuf[pidx<T>(j - 1)], b = lbuf[pidx<T>(M - j - 1)];
+        const cx<T> a = lbuf[pidx<T>((j - 1) ^ sw)], b = lbuf[pidx<T>((M - j - 1) ^ sw)];
         const T sj = sinl[j];
         const cx<T> sum = a + b, dif = a - b;
         v[s] = cx<T>{sj * sum.x + (T)0.5 * dif.x, sj * sum.y + (T)0.5 * dif.y};

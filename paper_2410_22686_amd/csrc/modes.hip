@@ -19,6 +19,9 @@
 //   [x2 in 3-D]
 //   rows out   transform along x1, combine w_1 = z_1 - z_2,
 //              w_2 = z_1 + z_2                               (mode_rows_out)
+// Up to nx = 63 a whole (x1, x2) plane fits the LDS of half a CU, and x1 and x2
+// are one pass on the way in and one on the way out (mode_plane_in, _out); in
+// 2-D only the recurrences are left between them.
 // The recurrence couples all steps of a mode, the transform all modes of a
 // line.  Where the lines of one step fill the chip, blocks march along a chunk
 // of steps with the state of their modes in registers: transform, accumulate
@@ -170,6 +173,168 @@ __global__ void __launch_bounds__(rows_out_threads(L)) mode_rows_out_kernel(Geo 
       } else {
         w1[pos - 1] = z1 - z2;
         w2[pos - 1] = z1 + z2;
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Planes of nx <= 63: both axes of an (x1, x2) plane in one pass, the plane in
+// LDS.  M groups of M/8 threads take a line each, so the block holds a whole
+// axis of its planes in registers between the two (64 lines of 8 threads at
+// nx = 63, 74 KB of LDS, two blocks per CU); the results of the rows are
+// written back transposed and the columns are rows then.  A pass is loads,
+// transforms and stores of one plane after another, two planes overlapping on a
+// CU: about 200 us at 3-D nx = 63, n = 100 (4 TB/s), where the rows took 227 and
+// 186 us and x2 151 more each way.  The whole preconditioner there 1119 -> 862
+// us; 2-D nx = 63, n = 100, four members 75 -> 59 us (n = 400, sixteen: 1013 ->
+// 726); nx = 31, n = 32 24.7 -> 18.9 us; 3-D nx = 15, n = 100, eight members
+// 263 -> 119 us.  At nx = 127 a plane (258 KB) does not fit.
+// ---------------------------------------------------------------------------
+// threads of a block: one plane, or one wave
+constexpr int plane_threads(int L) { return (L / 16) * (L / 2) < 64 ? 64 : (L / 16) * (L / 2); }
+
+template <class T, int L>
+struct PlaneTile {
+  using H = HalfDst<T, L>;
+  static constexpr int M = H::M, N = H::N, TM = H::TM, LD = line_ld(M);
+  static constexpr int TP = TM * M;               // threads of a plane
+  static constexpr int NT = plane_threads(L);
+  static constexpr int PPB = NT / TP;
+  static constexpr int QN = (N * N + TP - 1) / TP;  // elements per thread
+  // slot of (row, col): the TM lanes of a line write rows 8 apart of one
+  // column, which the row's XOR spreads over the banks
+  static __device__ __forceinline__ int slot(int row, int col) { return row * LD + pidx<T>(col ^ ((row >> 3) & 7)); }
+  static __device__ __forceinline__ void transform(cx<T>* plane, int tp, const cx<T>* twm, const T* sinl) {
+    const int lid = tp / TM, t = tp - lid * TM;
+    cx<T>* lbuf = plane + lid * LD;
+#pragma unroll 1
+    for (int ax = 0; ax < 2; ++ax) {
+      cx<T> v[8], o[8];
+      H::pre(v, t, lbuf, sinl, (lid >> 3) & 7);
+      RegStages<T, M, TM, -1, 1>::run(v, t, lbuf, twm);
+      H::post(v, o, t, lbuf);
+      __syncthreads();
+#pragma unroll
+      for (int r = 0; r < 8; ++r)
+        if (8 * t + r >= 1 && lid < N) plane[slot(8 * t + r - 1, lid)] = o[r];
+      __syncthreads();
+    }
+  }
+};
+
+template <class T, int L>
+__global__ void __launch_bounds__(plane_threads(L)) mode_plane_in_kernel(Geo g, const double* __restrict__ v,
+                                                                            cx<T>* __restrict__ c,
+                                                                            const cx<T>* __restrict__ twL,
+                                                                            const double* __restrict__ vscale,
+                                                                            int vs_stride, ModeParams mp) {
+  using P = PlaneTile<T, L>;
+  constexpr int M = P::M, N = P::N, TP = P::TP;
+  __shared__ cx<T> buf[P::PPB * M * P::LD];
+  __shared__ cx<T> twm[M];
+  __shared__ T sinl[M];
+  const int lp = threadIdx.x / TP, tp = threadIdx.x - lp * TP;
+  cx<T>* plane = buf + lp * M * P::LD;
+  const int nz = g.m / (N * N);  // planes per slice
+  const unsigned total = (unsigned)g.B * g.n * nz;
+  const unsigned pl = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * P::PPB + lp;
+  const unsigned sl = min(pl, total - 1) / nz;
+  const int iz = (int)(min(pl, total - 1) - sl * nz);
+  const int b = (int)(sl / g.n), s = (int)(sl - (unsigned)b * g.n);
+  const bool valid = pl < total && !(mp.active && !mp.active[b]);
+  if (__syncthreads_or(valid) == 0) return;
+  const double sc = mp.cnorm * (vscale ? vscale[(size_t)b * vs_stride] : 1.0);
+  const double* v1 = v + (size_t)b * g.vs + (size_t)(g.n - 1 - s) * g.m + (size_t)iz * N * N;
+  const double* v2 = v + (size_t)b * g.vs + (size_t)(g.n + s) * g.m + (size_t)iz * N * N;
+  double a1[P::QN], a2[P::QN];
+#pragma unroll
+  for (int q = 0; q < P::QN; ++q) {
+    const int e = min(tp + TP * q, N * N - 1);
+    a1[q] = v1[e];
+    a2[q] = v2[e];
+  }
+  for (int k = threadIdx.x; k < M; k += P::NT) {
+    twm[k] = twL[2 * k];
+    sinl[k] = -twL[k].y;
+  }
+#pragma unroll
+  for (int q = 0; q < P::QN; ++q) {
+    const int e = min(tp + TP * q, N * N - 1);
+    plane[P::slot(e / N, e % N)] = cx<T>{(T)(sc * a2[q]), (T)(sc * a1[q])};
+  }
+  __syncthreads();
+  P::transform(plane, tp, twm, sinl);
+  if (!valid) return;
+  cx<T>* out = c + (size_t)sl * g.m + (size_t)iz * N * N;
+#pragma unroll
+  for (int q = 0; q < P::QN; ++q) {
+    const int e = tp + TP * q;
+    if (e < N * N) out[e] = plane[P::slot(e / N, e % N)];
+  }
+}
+
+// w_1^s + i w_2^s is the transform of (z_1^s - z_2^s) + i (z_1^s + z_2^s), with
+// z_2^s the real part of slice s and z_1^s the imaginary part of slice
+// n - 1 - s; the planes of such a pair of slices are neighbours in the grid,
+// so that each finds the other's half of a line of memory in the L2.
+template <class T, int L, bool ACCUM>
+__global__ void __launch_bounds__(plane_threads(L)) mode_plane_out_kernel(Geo g, const cx<T>* __restrict__ c,
+                                                                             double* __restrict__ w,
+                                                                             const cx<T>* __restrict__ twL,
+                                                                             ModeParams mp) {
+  using P = PlaneTile<T, L>;
+  constexpr int M = P::M, N = P::N, TP = P::TP;
+  __shared__ cx<T> buf[P::PPB * M * P::LD];
+  __shared__ cx<T> twm[M];
+  __shared__ T sinl[M];
+  const int lp = threadIdx.x / TP, tp = threadIdx.x - lp * TP;
+  cx<T>* plane = buf + lp * M * P::LD;
+  const int nz = g.m / (N * N), npair = (g.n + 1) / 2;
+  const unsigned total = 2u * g.B * npair * nz;
+  const unsigned pl = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * P::PPB + lp;
+  const unsigned pz = min(pl, total - 1) / 2;  // (member, pair, plane)
+  const unsigned pr = pz / nz;
+  const int iz = (int)(pz - pr * nz);
+  const int b = (int)(pr / npair), p = (int)(pr - (unsigned)b * npair);
+  const int s = (pl & 1) ? g.n - 1 - p : p;
+  // the middle slice of an odd number is its own partner, written once
+  const bool valid = pl < total && !(mp.active && !mp.active[b]) && !((pl & 1) && s == p);
+  if (__syncthreads_or(valid) == 0) return;
+  const T* c2 = reinterpret_cast<const T*>(c + ((size_t)b * g.n + s) * g.m + (size_t)iz * N * N);
+  const T* c1 = reinterpret_cast<const T*>(c + ((size_t)b * g.n + (g.n - 1 - s)) * g.m + (size_t)iz * N * N) + 1;
+  T a1[P::QN], a2[P::QN];
+#pragma unroll
+  for (int q = 0; q < P::QN; ++q) {
+    const int e = min(tp + TP * q, N * N - 1);
+    a1[q] = c1[2 * e];
+    a2[q] = c2[2 * e];
+  }
+  for (int k = threadIdx.x; k < M; k += P::NT) {
+    twm[k] = twL[2 * k];
+    sinl[k] = -twL[k].y;
+  }
+#pragma unroll
+  for (int q = 0; q < P::QN; ++q) {
+    const int e = min(tp + TP * q, N * N - 1);
+    plane[P::slot(e / N, e % N)] = cx<T>{a1[q] - a2[q], a1[q] + a2[q]};
+  }
+  __syncthreads();
+  P::transform(plane, tp, twm, sinl);
+  if (!valid) return;
+  double* w1 = w + (size_t)b * g.vs + (size_t)s * g.m + (size_t)iz * N * N;
+  double* w2 = w1 + (size_t)g.n * g.m;
+#pragma unroll
+  for (int q = 0; q < P::QN; ++q) {
+    const int e = tp + TP * q;
+    if (e < N * N) {
+      const cx<T> z = plane[P::slot(e / N, e % N)];
+      if (ACCUM) {
+        w1[e] += (double)z.x;
+        w2[e] += (double)z.y;
+      } else {
+        w1[e] = (double)z.x;
+        w2[e] = (double)z.y;
       }
     }
   }
@@ -465,6 +630,7 @@ __global__ void __launch_bounds__(NT) mode_march_out_kernel(Geo g, cx<T>* __rest
 // for two rounds of the chip (1024), chunks of at least 8 steps (a chunk's end
 // and start values are two more slices each).
 static int march_chunks(const Geo& g) {
+  if (g.dim == 2 && g.nx <= 63) return 0;  // no axis left beyond the planes
   const int M = g.nx + 1, lpb = 256 / (M / 8);
   const long long tiles = ((long long)g.m / g.nx + lpb - 1) / lpb * g.B;
   const long long ch = std::max<long long>(1, (1024 + tiles - 1) / tiles);
@@ -487,15 +653,21 @@ static bool modes_L(const Geo& g, const double* v, double* w, cx<T>* c, cx<T>* e
   const int inner = g.m / g.nx;
   const double nm = (double)g.n * g.m * tb.nact;
   const double pass = 2.0 * sizeof(cx<T>) * nm;
-  {
+  constexpr bool PLANES = L <= 128;
+  tbeg(tb.timer, KF_DST_ROWS, (16.0 + sizeof(cx<T>)) * nm);
+  if constexpr (PLANES) {
+    using P = PlaneTile<T, L>;
+    const long long planes = nslices * (g.m / (P::N * P::N));
+    mode_plane_in_kernel<T, L><<<(unsigned)((planes + P::PPB - 1) / P::PPB), P::NT, 0, st>>>(g, v, c, twL, vscale,
+                                                                                             vs_stride, mp);
+  } else {
     constexpr int LPB = reg_threads(L) / (L / 8);
     const long long lines = nslices * inner;
-    tbeg(tb.timer, KF_DST_ROWS, (16.0 + sizeof(cx<T>)) * nm);
     mode_rows_in_kernel<T, L><<<(unsigned)((lines + LPB - 1) / LPB), reg_threads(L), 0, st>>>(g, v, c, twL, vscale,
                                                                                              vs_stride, mp);
-    tend(tb.timer);
   }
-  if (g.dim == 3 && !launch_dst_axis(g, c, fp32, tb, nslices, 2, st)) return false;
+  tend(tb.timer);
+  if (!PLANES && g.dim == 3 && !launch_dst_axis(g, c, fp32, tb, nslices, 2, st)) return false;
   const int CH = march_chunks(g);
   if (CH > 0) {
     constexpr int NT = 256, LPB = MarchTile<T, L, NT>::LPB;
@@ -515,7 +687,8 @@ static bool modes_L(const Geo& g, const double* v, double* w, cx<T>* c, cx<T>* e
     mode_march_out_kernel<T, L, NT><<<grid, NT, 0, st>>>(g, c, ends, twL, tiles, chunks, len, mp);
     tend(tb.timer);
   } else {
-    if (!launch_dst_axis(g, c, fp32, tb, nslices, g.dim == 3 ? 3 : 2, st)) return false;
+    const bool axis = !PLANES || g.dim == 3;  // a last axis beyond the planes
+    if (axis && !launch_dst_axis(g, c, fp32, tb, nslices, g.dim == 3 ? 3 : 2, st)) return false;
     tbeg(tb.timer, KF_MODES, pass);
     // 64 waves' worth of modes per XCD and more need no split in time
     if ((long long)g.m * g.B >= 65536)
@@ -523,18 +696,24 @@ static bool modes_L(const Geo& g, const double* v, double* w, cx<T>* c, cx<T>* e
     else
       mode_scan_kernel<T, 16><<<dim3((g.m + 15) / 16, g.B), 256, 0, st>>>(g, c, mp);
     tend(tb.timer);
-    if (!launch_dst_axis(g, c, fp32, tb, nslices, g.dim == 3 ? 3 : 2, st)) return false;
+    if (axis && !launch_dst_axis(g, c, fp32, tb, nslices, g.dim == 3 ? 3 : 2, st)) return false;
   }
-  if (g.dim == 3 && !launch_dst_axis(g, c, fp32, tb, nslices, 2, st)) return false;
-  {
+  if (!PLANES && g.dim == 3 && !launch_dst_axis(g, c, fp32, tb, nslices, 2, st)) return false;
+  tbeg(tb.timer, KF_DST_ROWS, (sizeof(cx<T>) + (accum ? 32.0 : 16.0)) * nm);
+  if constexpr (PLANES) {
+    using P = PlaneTile<T, L>;
+    const long long planes = 2LL * g.B * ((g.n + 1) / 2) * (g.m / (P::N * P::N));
+    const unsigned grid = (unsigned)((planes + P::PPB - 1) / P::PPB);
+    if (accum) mode_plane_out_kernel<T, L, true><<<grid, P::NT, 0, st>>>(g, c, w, twL, mp);
+    else mode_plane_out_kernel<T, L, false><<<grid, P::NT, 0, st>>>(g, c, w, twL, mp);
+  } else {
     constexpr int NT = rows_out_threads(L), PL = NT / (L / 8) / 2;
     const long long pairs = (long long)g.B * ((g.n + 1) / 2) * inner;
     const unsigned grid = (unsigned)((pairs + PL - 1) / PL);
-    tbeg(tb.timer, KF_DST_ROWS, (sizeof(cx<T>) + (accum ? 32.0 : 16.0)) * nm);
     if (accum) mode_rows_out_kernel<T, L, true><<<grid, NT, 0, st>>>(g, c, w, twL, mp);
     else mode_rows_out_kernel<T, L, false><<<grid, NT, 0, st>>>(g, c, w, twL, mp);
-    tend(tb.timer);
   }
+  tend(tb.timer);
   return true;
 }
 
