@@ -194,12 +194,13 @@ __device__ __forceinline__ void odd_extend(cx<T> (&v)[8], int t, cx<T>* lbuf) {
   }
 }
 
-// contiguous lines (x1): each line's values go straight between HBM and registers
+// contiguous lines (x1): each line's values go straight between HBM and registers,
+// the odd extension's second half through LDS (FP32 2-D nx = 255, n = 255, two
+// members 168 us per pass with it loaded a second time, 152 us so)
 template <class T, int L, int DIVIDE_>
 __global__ void __launch_bounds__(reg_threads(L)) dst_reg_kernel(Geo g, cx<T>* __restrict__ data, LineGeom lg,
                                                                  const cx<T>* __restrict__ twL, DivideParams dp) {
   constexpr bool DIVIDE = DIVIDE_ != 0;
-  constexpr int N = L / 2 - 1;
   constexpr int TL = L / 8;
   constexpr int LPB = reg_threads(L) / TL;
   constexpr int LD = line_ld(L);
@@ -217,23 +218,17 @@ __global__ void __launch_bounds__(reg_threads(L)) dst_reg_kernel(Geo g, cx<T>* _
   const int line = l0 + lid;
   const bool valid = line < lg.lines;
   cx<T>* lbuf = buf + lid * LD;
-  auto zval = [&](int e) -> cx<T> {
-    if (!valid) return cx<T>{0, 0};
-    return data[pbase + (long long)line * lg.line_stride + (long long)e * lg.elem_stride];
-  };
+  // positions t + TL s, s < 4: 0 .. N; the second half of the odd extension
+  // mirrors them through LDS
   cx<T> v[8];
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
+  for (int s = 0; s < 4; ++s) {
     const int pos = t + TL * s;
-    if (pos >= 1 && pos <= N) {
-      v[s] = zval(pos - 1);
-    } else if (pos >= N + 2) {
-      const cx<T> z = zval(L - 1 - pos);
-      v[s] = cx<T>{-z.x, -z.y};
-    } else {
-      v[s] = cx<T>{0, 0};
-    }
+    v[s] = valid && pos != 0
+               ? data[pbase + (long long)line * lg.line_stride + (long long)(pos - 1) * lg.elem_stride]
+               : cx<T>{0, 0};
   }
+  mirror<T, L, TL>(v, t, lbuf);
   RegStages<T, L, TL, -1, 1>::run(v, t, lbuf, twL);
   if (DIVIDE) {
     divide_line<T, L, TL>(v, t, g, dp, plane, line, valid);
@@ -241,9 +236,9 @@ __global__ void __launch_bounds__(reg_threads(L)) dst_reg_kernel(Geo g, cx<T>* _
     RegStages<T, L, TL, -1, 1>::run(v, t, lbuf, twL);
   }
 #pragma unroll
-  for (int s = 0; s < 8; ++s) {
+  for (int s = 0; s < 4; ++s) {
     const int pos = t + TL * s;
-    if (pos >= 1 && pos <= N && valid)
+    if (pos >= 1 && valid)
       data[pbase + (long long)line * lg.line_stride + (long long)(pos - 1) * lg.elem_stride] = v[s];
   }
 }

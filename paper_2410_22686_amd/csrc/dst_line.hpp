@@ -108,6 +108,22 @@ struct RegStages {
   }
 };
 
+// the odd extension's second half, positions t + TL k for k = 4..7, from the
+// first (position p mirrors L - p; positions 0 and N + 1 hold zero)
+template <class T, int L, int TL>
+__device__ __forceinline__ void mirror(cx<T> (&z)[8], int t, cx<T>* lbuf) {
+  line_sync<TL>();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) lbuf[pidx<T>(t + TL * k)] = z[k];
+  line_sync<TL>();
+#pragma unroll
+  for (int k = 4; k < 8; ++k) {
+    const int pos = t + TL * k;
+    const cx<T> q = lbuf[pidx<T>(pos == L / 2 ? 0 : L - pos)];
+    z[k] = cx<T>{-q.x, -q.y};
+  }
+}
+
 // threads per block of the register row kernel: 128 from L = 512 on (two
 // lines of 64 threads, or one line of 128 at L = 1024, where the block's
 // exchanges then wait on two wavefronts instead of four: measured 5% faster

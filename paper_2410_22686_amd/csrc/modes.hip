@@ -67,22 +67,6 @@ __device__ __forceinline__ double ipow(double x, int n) {
 // from memory the pass in took 1.30 instead of 1.14 ms, the pass out 1.03
 // instead of 0.94, 2-D nx = 511, n = 511).  HBM-bound: 3.8 and 4.6 TB/s.
 // ---------------------------------------------------------------------------
-// the odd extension's second half, positions t + TL k for k = 4..7, from the
-// first (position p mirrors L - p; positions 0 and N + 1 hold zero)
-template <class T, int L, int TL>
-__device__ __forceinline__ void mirror(cx<T> (&z)[8], int t, cx<T>* lbuf) {
-  line_sync<TL>();
-#pragma unroll
-  for (int k = 0; k < 4; ++k) lbuf[pidx<T>(t + TL * k)] = z[k];
-  line_sync<TL>();
-#pragma unroll
-  for (int k = 4; k < 8; ++k) {
-    const int pos = t + TL * k;
-    const cx<T> q = lbuf[pidx<T>(pos == L / 2 ? 0 : L - pos)];
-    z[k] = cx<T>{-q.x, -q.y};
-  }
-}
-
 template <class T, int L>
 __global__ void __launch_bounds__(reg_threads(L)) mode_rows_in_kernel(Geo g, const double* __restrict__ v,
                                                                       cx<T>* __restrict__ c,
