@@ -62,49 +62,88 @@ __device__ __forceinline__ double ipow(double x, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// contiguous lines, register-resident (as dst_reg_kernel): TL = L/8 threads
-// per line.  The odd extension's second half goes through LDS (loaded twice
-// from memory the pass in took 1.30 instead of 1.14 ms, the pass out 1.03
-// instead of 0.94, 2-D nx = 511, n = 511).  HBM-bound: 3.8 and 4.6 TB/s.
+// contiguous lines, M/8 threads each (one wavefront or a part of it, so that
+// no line waits on another): half-length transforms as in dst_half_kernel, the
+// line staged in LDS on either side so that loads and stores are coalesced.
+// Persistent blocks, the tables in LDS.  HBM-bound at the rate of a copy: 2-D
+// nx = 511, n = 511 884 us (4.8 TB/s); the register-resident full-length lines of
+// rows out took 1217 us here, nx = 127, n = 127, sixteen members 288 against 210.
 // ---------------------------------------------------------------------------
+constexpr int kRowThreads = 256;
 template <class T, int L>
-__global__ void __launch_bounds__(reg_threads(L)) mode_rows_in_kernel(Geo g, const double* __restrict__ v,
-                                                                      cx<T>* __restrict__ c,
-                                                                      const cx<T>* __restrict__ twL,
-                                                                      const double* __restrict__ vscale, int vs_stride,
-                                                                      ModeParams mp) {
-  constexpr int N = L / 2 - 1, TL = L / 8, NT = reg_threads(L), LPB = NT / TL, LD = line_ld(L);
-  __shared__ cx<T> buf[LPB * LD];
-  const int lid = threadIdx.x / TL, t = threadIdx.x - lid * TL;
-  const int inner = g.m / N;  // lines per slice
-  // 32 bits hold the number of lines (2^32 of 7 points would be 480 GB)
-  const unsigned total = (unsigned)g.B * g.n * inner;
-  const unsigned ln = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * LPB + lid;
-  const unsigned sl = min(ln, total - 1) / inner;
-  const int li = (int)(min(ln, total - 1) - sl * inner);
-  const int b = (int)(sl / g.n), s = (int)(sl - (unsigned)b * g.n);
-  const bool valid = ln < total && !(mp.active && !mp.active[b]);
-  if (__syncthreads_or(valid) == 0) return;
-  const double sc = mp.cnorm * (vscale ? vscale[(size_t)b * vs_stride] : 1.0);
-  const double* v1 = v + (size_t)b * g.vs + (size_t)(g.n - 1 - s) * g.m + (size_t)li * N;
-  const double* v2 = v + (size_t)b * g.vs + (size_t)(g.n + s) * g.m + (size_t)li * N;
-  cx<T> z[8];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int pos = t + TL * k;
-    z[k] = valid && pos != 0 ? cx<T>{(T)(sc * v2[pos - 1]), (T)(sc * v1[pos - 1])} : cx<T>{0, 0};
+struct RowLines {
+  using H = HalfDst<T, L>;
+  static constexpr int M = H::M, N = H::N, TM = H::TM, NT = kRowThreads, LPB = NT / TM;
+  static constexpr int LD = M >= 128 ? M + 4 : line_ld(M);
+  static __device__ __forceinline__ void tables(const cx<T>* __restrict__ twL, cx<T>* twm, T* sinl) {
+    for (int k = threadIdx.x; k < M; k += NT) {
+      twm[k] = twL[2 * k];
+      sinl[k] = -twL[k].y;
+    }
+    __syncthreads();
   }
-  mirror<T, L, TL>(z, t, buf + lid * LD);
-  RegStages<T, L, TL, -1, 1>::run(z, t, buf + lid * LD, twL);
-  if (!valid) return;
-  cx<T>* out = c + (size_t)sl * g.m + (size_t)li * N;
+  // the line's elements t + TM k in z[k] to those of its transform, through lbuf
+  static __device__ __forceinline__ void transform(cx<T> (&z)[8], int t, cx<T>* lbuf, const cx<T>* twm, const T* sinl) {
+    line_sync<TM>();
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int pos = t + TL * k;
-    if (pos >= 1) out[pos - 1] = z[k];
+    for (int k = 0; k < 8; ++k) lbuf[pidx<T>(t + TM * k)] = z[k];
+    line_sync<TM>();
+    cx<T> v[8];
+    H::pre(v, t, lbuf, sinl);
+    RegStages<T, M, TM, -1, 1>::run(v, t, lbuf, twm);
+    H::post(v, z, t, lbuf);
+    line_sync<TM>();
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      if (8 * t + r >= 1) lbuf[pidx<T>(8 * t + r - 1)] = z[r];
+    line_sync<TM>();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) z[k] = lbuf[pidx<T>(t + TM * k)];
+  }
+};
+
+template <class T, int L>
+__global__ void __launch_bounds__(kRowThreads) mode_rows_in_kernel(Geo g, const double* __restrict__ v,
+                                                                   cx<T>* __restrict__ c,
+                                                                   const cx<T>* __restrict__ twL,
+                                                                   const double* __restrict__ vscale, int vs_stride,
+                                                                   ModeParams mp) {
+  using R = RowLines<T, L>;
+  constexpr int N = R::N, TM = R::TM, LPB = R::LPB;
+  __shared__ cx<T> buf[LPB * R::LD];
+  __shared__ cx<T> twm[R::M];
+  __shared__ T sinl[R::M];
+  R::tables(twL, twm, sinl);
+  const int lid = threadIdx.x / TM, t = threadIdx.x - lid * TM;
+  const int inner = g.m / N;  // lines per slice
+  // 32 bits hold the number of lines (2^32 of 127 points would be 4 TB)
+  const unsigned total = (unsigned)g.B * g.n * inner;
+  for (unsigned ln = (unsigned)xcd_remap(blockIdx.x, gridDim.x) * LPB + lid; ln < total; ln += gridDim.x * LPB) {
+    const unsigned sl = ln / inner;
+    const int li = (int)(ln - sl * inner);
+    const int b = (int)(sl / g.n), s = (int)(sl - (unsigned)b * g.n);
+    if (mp.active && !mp.active[b]) continue;
+    const double sc = mp.cnorm * (vscale ? vscale[(size_t)b * vs_stride] : 1.0);
+    const double* v1 = v + (size_t)b * g.vs + (size_t)(g.n - 1 - s) * g.m + (size_t)li * N;
+    const double* v2 = v + (size_t)b * g.vs + (size_t)(g.n + s) * g.m + (size_t)li * N;
+    cx<T> z[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int e = min(t + TM * k, N - 1);
+      z[k] = cx<T>{(T)(sc * v2[e]), (T)(sc * v1[e])};
+    }
+    R::transform(z, t, buf + lid * R::LD, twm, sinl);
+    cx<T>* out = c + (size_t)sl * g.m + (size_t)li * N;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (t + TM * k < N) out[t + TM * k] = z[k];
   }
 }
 
+// Rows out keeps lines of L/8 threads in registers (as dst_reg_kernel), one pass
+// per block: with half-length lines and the pair's sum and difference formed
+// before the transform, each line read half of two lines, and the pass took as
+// long at nx = 511 (1036 against 1053 us), 127 (239, 239) and longer at 255.
 // threads per block of rows out: the two lines of a pair at least
 constexpr int rows_out_threads(int L) { return reg_threads(L) > 2 * (L / 8) ? reg_threads(L) : 2 * (L / 8); }
 
@@ -645,10 +684,11 @@ static bool modes_L(const Geo& g, const double* v, double* w, cx<T>* c, cx<T>* e
     mode_plane_in_kernel<T, L><<<(unsigned)((planes + P::PPB - 1) / P::PPB), P::NT, 0, st>>>(g, v, c, twL, vscale,
                                                                                              vs_stride, mp);
   } else {
-    constexpr int LPB = reg_threads(L) / (L / 8);
+    constexpr int LPB = RowLines<T, L>::LPB;
     const long long lines = nslices * inner;
-    mode_rows_in_kernel<T, L><<<(unsigned)((lines + LPB - 1) / LPB), reg_threads(L), 0, st>>>(g, v, c, twL, vscale,
-                                                                                             vs_stride, mp);
+    static const int res = resident_blocks(mode_rows_in_kernel<T, L>, kRowThreads, 0);
+    const unsigned grid = (unsigned)std::min<long long>((lines + LPB - 1) / LPB, (long long)res * std::max(1, tb.ncu));
+    mode_rows_in_kernel<T, L><<<grid, kRowThreads, 0, st>>>(g, v, c, twL, vscale, vs_stride, mp);
   }
   tend(tb.timer);
   if (!PLANES && g.dim == 3 && !launch_dst_axis(g, c, fp32, tb, nslices, 2, st)) return false;
