@@ -270,15 +270,16 @@ pcop_status pcop_precond_apply(pcop_ctx ctx, const double* v, double* w);
  * hand the library scratch per call: code under HIP graph capture, tight
  * serving loops.  The spectrum scratch is not the context's workspace but a
  * file-scope device array of the library, one per device, held until the
- * process ends; the call itself allocates nothing and does no per-kernel
- * timing.
+ * process ends (the values that chunks of steps hand on, where the apply goes
+ * by modes, are in the context's workspace); the call itself allocates
+ * nothing and does no per-kernel timing.
  *   Limit: the spectrum, 2 (n/2 + 1) m complex values per member (16 bytes
  *   each in FP64, 8 with PCOP_MIXED), must fit 64 MiB; larger contexts get
  *   PCOP_ERR_UNSUPPORTED, as do contexts with PCOP_MG or
  *   PCOP_PRECOND_IDEAL.  The current device must be the one current at
  *   pcop_setup (PCOP_ERR_INVALID_ARG otherwise).
  *   Sharing: every call on a device uses that device's one array (the
- *   forward time pass writes all of it before it is read, so nothing needs
+ *   first pass writes all of it that is read later, so nothing needs
  *   clearing); calls that overlap in time on one device -- from different
  *   streams, contexts or threads -- race and must be serialised by the
  *   caller.
