@@ -339,15 +339,23 @@ def _compose_cpu(cfg, iters, pb, t_start, threads, cores, t_mv, n_mv, t_dft, m_d
 
 def precond_stats(stats, precision, cfg):
     """The preconditioner's passes (time forward, spatial solves, time
-    inverse) of one leg: their algorithmic bytes over their summed time."""
+    inverse; or the passes by modes) of one leg: their algorithmic bytes over
+    their summed time."""
     pre = {k: v for k, v in stats.items() if k in PRECOND_FAMILIES}
     pre_ms = sum(v["ms"] for v in pre.values())
     pre_bytes = sum(v["bytes"] for v in pre.values())
-    if pre_ms <= 0 or "time_fwd" not in pre:
-        return None
     csz = 16.0 if precision == "fp64" else 8.0
-    per_member = 8.0 * 2 * cfg.n * cfg.m + csz * 2 * (cfg.n // 2 + 1) * cfg.m
-    member_applies = pre["time_fwd"]["bytes"] / per_member
+    if pre_ms <= 0:
+        return None
+    if "time_fwd" in pre:
+        per_member = 8.0 * 2 * cfg.n * cfg.m + csz * 2 * (cfg.n // 2 + 1) * cfg.m
+        member_applies = pre["time_fwd"]["bytes"] / per_member
+    elif "modes" in pre:
+        # by modes: the last axis there and back, or (2-D planes) the recurrences
+        last = pre.get("dst_last_solve")
+        member_applies = (last["bytes"] / 2 if last else pre["modes"]["bytes"]) / (2 * csz * cfg.n * cfg.m)
+    else:
+        return None
     return {"achieved_pass_bytes_GBs": round(pre_bytes / (pre_ms * 1e-3) / 1e9, 1),
             "frac": round(pre_bytes / (pre_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
             "member_applies": round(member_applies, 2),
