@@ -53,12 +53,30 @@ __device__ __forceinline__ double mode_mu(const Geo& g, const double* mu1, int i
   return mu;
 }
 
-// x^n for n >= 0
-__device__ __forceinline__ double ipow(double x, int n) {
-  double r = 1.0;
-  for (; n > 0; n >>= 1, x *= x)
-    if (n & 1) r *= x;
-  return r;
+// 1/d for d = 1 + delta in two doubles.  With hi = fl(1/d) alone every step
+// of a recurrence makes the same relative error, which n steps add up, and a
+// small delta would be lost to the rounding of 1 + delta; hi + lo is 1/d to
+// twice the precision and costs one multiplication per value.  FP32 slices
+// are far coarser than that error and take hi alone.
+template <class T>
+struct ModeRecip {
+  double hi, lo;
+  __device__ __forceinline__ double operator()(double a) const { return sizeof(T) == 8 ? fma(a, hi, a * lo) : a * hi; }
+};
+template <class T>
+__device__ __forceinline__ ModeRecip<T> mode_recip(double delta) {
+  const double d = 1.0 + delta, t = d - 1.0;
+  const double rest = (1.0 - (d - t)) + (delta - t);  // 1 + delta - d
+  const double hi = 1.0 / d;
+  return ModeRecip<T>{hi, fma(-hi, rest, fma(-hi, d, 1.0)) * hi};
+}
+// d^{-n}
+__device__ __forceinline__ double mode_decay(double delta, int n) { return exp(-n * log1p(delta)); }
+// eps / (1 - eps d^{-n}) without the cancellation where eps and d^{-n} are
+// close to 1 (a short horizon): formed from rounded powers, eps = 1, n = 511,
+// T = 1e-4 left 2e-12 of the result, against 6e-16 now (four steps: 3e-16)
+__device__ __forceinline__ double mode_close(double delta, int n, double eps) {
+  return eps / ((1.0 - eps) - eps * expm1(-n * log1p(delta)));
 }
 
 // ---------------------------------------------------------------------------
@@ -384,7 +402,8 @@ __global__ void __launch_bounds__(256) mode_scan_kernel(Geo g, cx<T>* __restrict
   const int n = g.n, m = g.m, nx = g.nx;
   const bool in = i < m;
   const int im = in ? i : m - 1;
-  const double rd = 1.0 / ((1.0 + mp.alpha[b]) + g.tau * mode_mu(g, mp.mu1, im));
+  const double delta = mp.alpha[b] + g.tau * mode_mu(g, mp.mu1, im);
+  const ModeRecip<T> rd = mode_recip<T>(delta);
   double f = 1.0;
   if (mp.im1) {
     f = mp.im1[im % nx] * mp.im1[(im / nx) % nx];
@@ -401,8 +420,8 @@ __global__ void __launch_bounds__(256) mode_scan_kernel(Geo g, cx<T>* __restrict
 #pragma unroll
       for (int u = 0; u < kScanAhead; ++u)
         if (s + u < s1) {
-          z.x = (f * (double)y[u].x + z.x) * rd;
-          z.y = (f * (double)y[u].y + z.y) * rd;
+          z.x = rd(f * (double)y[u].x + z.x);
+          z.y = rd(f * (double)y[u].y + z.y);
           put(s + u, z);
         }
     }
@@ -412,19 +431,19 @@ __global__ void __launch_bounds__(256) mode_scan_kernel(Geo g, cx<T>* __restrict
   if (CH > 1 || mp.eps != 0.0) {
     ends[q][k] = walk(z, [](int, cx<double>) {});
     __syncthreads();
-    // chunk p passes on ends + rd^{its length} times what it got
-    const double decay = ipow(rd, len);
+    // chunk p passes on ends + d^{-its length} times what it got
+    const double decay = mode_decay(delta, len);
     auto chain = [&](cx<double> a, int upto) {
       for (int p = 0; p < upto; ++p) {
         const int lp = max(0, min(n - p * len, len));
-        const double dp = lp == len ? decay : ipow(rd, lp);
+        const double dp = lp == len ? decay : mode_decay(delta, lp);
         a = cx<double>{ends[p][k].x + dp * a.x, ends[p][k].y + dp * a.y};
       }
       return a;
     };
     if (mp.eps != 0.0) {
       const cx<double> S = chain(z, CH);
-      const double close = mp.eps / (1.0 - mp.eps * ipow(rd, n));
+      const double close = mode_close(delta, n, mp.eps);
       z = cx<double>{close * S.x, close * S.y};
     }
     z = chain(z, q);
@@ -436,8 +455,8 @@ __global__ void __launch_bounds__(256) mode_scan_kernel(Geo g, cx<T>* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Marching passes of the last axis.  HBM-bound with two blocks per CU (about 200
-// registers): 0.98 ms each at 2-D nx = 511, n = 511 (4.4 TB/s), where the
+// Marching passes of the last axis.  HBM-bound with two blocks per CU (210 to
+// 252 registers): 0.98 ms each at 2-D nx = 511, n = 511 (4.4 TB/s), where the
 // strided pass with the division and the two time transforms they replace took
 // 2.0 + 1.2 + 1.2 ms.  A tile is LPB neighbouring lines (M/8
 // threads each, half-length transforms as dst_half_kernel); a block takes one
@@ -492,7 +511,7 @@ __device__ __forceinline__ MarchBlock march_block(int tiles, int CH) {
 // the factor of their right-hand sides
 template <class T, int N, bool FEM>
 __device__ __forceinline__ void mode_factors(const Geo& g, const ModeParams& mp, int b, int line, int t,
-                                             double (&rd)[8], double (&f)[8]) {
+                                             ModeRecip<T> (&rd)[8], double (&f)[8]) {
   double ml = mp.mu1[line % g.nx], psl = FEM ? mp.im1[line % g.nx] : 1.0;
   if (g.dim == 3) {
     ml += mp.mu1[(line / g.nx) % g.nx];
@@ -501,7 +520,7 @@ __device__ __forceinline__ void mode_factors(const Geo& g, const ModeParams& mp,
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
     const int e = max(8 * t + r - 1, 0);
-    rd[r] = 1.0 / ((1.0 + mp.alpha[b]) + g.tau * (ml + mp.mu1[min(e, N - 1)]));
+    rd[r] = mode_recip<T>(mp.alpha[b] + g.tau * (ml + mp.mu1[min(e, N - 1)]));
     f[r] = FEM ? psl * mp.im1[min(e, N - 1)] : 1.0;
   }
 }
@@ -526,7 +545,8 @@ __global__ void __launch_bounds__(NT) mode_march_in_kernel(Geo g, cx<T>* __restr
   const int l0 = mb.tile * LPB, lid = threadIdx.x / TM, t = threadIdx.x - lid * TM;
   const int s0 = mb.q * len, s1 = min(g.n, s0 + len);
   cx<T>* lbuf = buf + lid * LD;
-  double rd[8], f[8];
+  ModeRecip<T> rd[8];
+  double f[8];
   mode_factors<T, N, FEM>(g, mp, mb.b, min(l0 + lid, lines - 1), t, rd, f);
   cx<double> z[8];
 #pragma unroll
@@ -550,7 +570,7 @@ __global__ void __launch_bounds__(NT) mode_march_in_kernel(Geo g, cx<T>* __restr
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       if (FEM) o[r] = cx<T>{(T)(f[r] * (double)o[r].x), (T)(f[r] * (double)o[r].y)};
-      z[r] = cx<double>{((double)o[r].x + z[r].x) * rd[r], ((double)o[r].y + z[r].y) * rd[r]};
+      z[r] = cx<double>{rd[r]((double)o[r].x + z[r].x), rd[r]((double)o[r].y + z[r].y)};
     }
     put(o);
     M_::store(cs, l0, lines, lines, buf);
@@ -569,8 +589,8 @@ template <class T>
 __global__ void __launch_bounds__(256) mode_chain_kernel(Geo g, cx<T>* __restrict__ ends, int CH, int len, ModeParams mp) {
   const int b = blockIdx.y, i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= g.m || (mp.active && !mp.active[b])) return;
-  const double rd = 1.0 / ((1.0 + mp.alpha[b]) + g.tau * mode_mu(g, mp.mu1, i));
-  const double decay = ipow(rd, len), last = ipow(rd, g.n - (CH - 1) * len);
+  const double delta = mp.alpha[b] + g.tau * mode_mu(g, mp.mu1, i);
+  const double decay = mode_decay(delta, len), last = mode_decay(delta, g.n - (CH - 1) * len);
   cx<T>* e = ends + (size_t)b * CH * g.m + i;
   cx<double> z{0.0, 0.0};
   if (mp.eps != 0.0) {
@@ -579,7 +599,7 @@ __global__ void __launch_bounds__(256) mode_chain_kernel(Geo g, cx<T>* __restric
       const cx<T> a = e[(size_t)q * g.m];
       z = cx<double>{(double)a.x + d * z.x, (double)a.y + d * z.y};
     }
-    const double close = mp.eps / (1.0 - mp.eps * ipow(rd, g.n));
+    const double close = mode_close(delta, g.n, mp.eps);
     z = cx<double>{close * z.x, close * z.y};
   }
   for (int q = 0; q < CH; ++q) {
@@ -610,7 +630,8 @@ __global__ void __launch_bounds__(NT) mode_march_out_kernel(Geo g, cx<T>* __rest
   const int l0 = mb.tile * LPB, lid = threadIdx.x / TM, t = threadIdx.x - lid * TM;
   const int s0 = mb.q * len, s1 = min(g.n, s0 + len);
   cx<T>* lbuf = buf + lid * LD;
-  double rd[8], f[8];
+  ModeRecip<T> rd[8];
+  double f[8];
   mode_factors<T, N, false>(g, mp, mb.b, min(l0 + lid, lines - 1), t, rd, f);
   M_::load(starts + ((size_t)mb.b * CH + mb.q) * g.m, l0, lines, lines, buf);
   __syncthreads();
@@ -630,7 +651,7 @@ __global__ void __launch_bounds__(NT) mode_march_out_kernel(Geo g, cx<T>* __rest
     for (int r = 0; r < 8; ++r)
       if (8 * t + r >= 1) {
         cx<T>& y = lbuf[pidx<T>(8 * t + r - 1)];
-        z[r] = cx<double>{((double)y.x + z[r].x) * rd[r], ((double)y.y + z[r].y) * rd[r]};
+        z[r] = cx<double>{rd[r]((double)y.x + z[r].x), rd[r]((double)y.y + z[r].y)};
         y = cx<T>{(T)z[r].x, (T)z[r].y};
       }
     line_sync<TM>();
