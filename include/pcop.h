@@ -166,9 +166,11 @@ typedef struct {
  *   precond    PCOP_PRECOND_EPS: the epsilon-circulant RBD preconditioner
  *              P_eps (Section 2.1; all time levels at once);
  *              PCOP_PRECOND_IDEAL: the ideal RBD preconditioner P of
- *              eq. matrix_P, applied by sequential substitution in time
- *              (n dependent spatial solves with (1 + alpha) I + tau K; the
- *              comparison method of Tables 4 and 8).  time_cols is ignored.
+ *              eq. matrix_P (the comparison method of Tables 4 and 8).  With
+ *              PCOP_DST, nx >= 7 and dst_kernel = 0 by recurrences along time
+ *              in the sine modes, else by sequential substitution in time (n
+ *              dependent spatial solves with (1 + alpha) I + tau K).
+ *              time_cols is ignored.
  *   kkt_jchunk KKT matvec kernel: 0 automatic (-8, on small grids fewer
  *              levels, or the tuner's choice);
  *              1..64 one thread per point marching that many time levels;

@@ -258,18 +258,17 @@ void plan_layout(const pcop_problem* p, const pcop_options* o, Layout& L) {
   }
   {
     // sine transforms with automatic kernels run by modes: the ideal
-    // preconditioner, and the epsilon-circulant one in FP64 (its FP32 form
-    // keeps the time transforms: the last steps of a mixed solve follow the
-    // FP32 rounding, and with it the operations)
+    // preconditioner (which never reads time_cols), and the epsilon-circulant
+    // one in FP64 (its FP32 form keeps the time transforms: the last steps of a
+    // mixed solve follow the FP32 rounding, and with it the operations)
     Geo g{};
     g.dim = d;
     g.nx = nx;
     g.n = n;
     g.m = (int)m;
     g.B = B;
-    const bool automatic = o->time_cols == 0 && o->dst_kernel == 0;
-    L.by_modes = o->spatial == PCOP_DST && modes_exist(g) &&
-                 (o->precond == PCOP_PRECOND_IDEAL || (automatic && !fp32));
+    L.by_modes = o->spatial == PCOP_DST && o->dst_kernel == 0 && modes_exist(g) &&
+                 (o->precond == PCOP_PRECOND_IDEAL || (o->time_cols == 0 && !fp32));
     if (L.by_modes) L.ends = take(L, mode_ends_bytes(g, fp32));
   }
   L.mg_levels = 0;

@@ -1,0 +1,42 @@
+"""The ideal preconditioner's two routes: with an explicit dst_kernel the
+sequential substitution runs on the sine-transform kernels that were asked for,
+with dst_kernel = 0 the recurrences by modes.
+
+Both are backward stable solves of the same systems: 1e-12 of the oracle's, and
+1e-5 with FP32 transforms, as in the other tests of this preconditioner."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import discretize as D, precond as P
+from paper_2410_22686_amd import Solver
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def families(s, v):
+    s.timing_enable(True)
+    w = s.precond_apply(v)
+    stats = s.timing_read()
+    s.timing_enable(False)
+    return w, set(stats)
+
+
+@pytest.mark.parametrize("dim,nx,nt,batch", [(2, 7, 5, 2), (2, 31, 6, 1), (3, 7, 4, 1), (3, 15, 3, 2)])
+@pytest.mark.parametrize("dst_kernel", [0, 1, 2, 3, 4, 5])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_ideal_honours_dst_kernel(dim, nx, nt, batch, dst_kernel, precision):
+    gammas = [10.0 ** (-2 - 3 * b) for b in range(batch)]
+    print(f"ideal route {precision} {dim} {nx} {nt} {batch} dst_kernel {dst_kernel}", flush=True)
+    s = Solver(dim, nx, nt, gammas, precision=precision, side="flexible" if precision == "mixed" else "right",
+               precond="ideal", dst_kernel=dst_kernel, restart=1, device=DEV)
+    v = W.random_vector(dim, nx, nt, seed=31, batch=batch)
+    w, names = families(s, torch.tensor(v, device=DEV))
+    assert ("modes" in names) == (dst_kernel == 0)
+    assert ("ideal_step" in names) == (dst_kernel != 0)
+    tol = 1e-5 if precision == "mixed" else 1e-12
+    for b, gm in enumerate(gammas):
+        wo = P.IdealRBD(D.make_problem(dim, nx, nt, gm)).apply(v[b].ravel())
+        assert np.linalg.norm(w[b].cpu().numpy().ravel() - wo) <= tol * np.linalg.norm(wo)
