@@ -168,8 +168,9 @@ typedef struct {
  *              PCOP_PRECOND_IDEAL: the ideal RBD preconditioner P of
  *              eq. matrix_P (the comparison method of Tables 4 and 8).  With
  *              PCOP_DST, nx >= 7 and dst_kernel = 0 by recurrences along time
- *              in the sine modes, else by sequential substitution in time (n
- *              dependent spatial solves with (1 + alpha) I + tau K).
+ *              in the sine modes (nt = 2 up to nx = 127), else by sequential
+ *              substitution in time (n dependent spatial solves with
+ *              (1 + alpha) I + tau K).
  *              time_cols is ignored.
  *   kkt_jchunk KKT matvec kernel: 0 automatic (-8, on small grids fewer
  *              levels, or the tuner's choice);

@@ -267,7 +267,12 @@ void plan_layout(const pcop_problem* p, const pcop_options* o, Layout& L) {
     g.n = n;
     g.m = (int)m;
     g.B = B;
-    L.by_modes = o->spatial == PCOP_DST && o->dst_kernel == 0 && modes_exist(g) &&
+    // One level of the ideal preconditioner is one spatial solve, whose last
+    // axis is one pass there and back: by modes it takes two passes and the
+    // recurrence's (2-D nx = 255 38 us against 26, nx = 511 40 against 37).  Up
+    // to nx = 127 the launches are all there is (30 us against 32).
+    const bool one_solve = o->precond == PCOP_PRECOND_IDEAL && n == 1 && nx > 127;
+    L.by_modes = o->spatial == PCOP_DST && o->dst_kernel == 0 && modes_exist(g) && !one_solve &&
                  (o->precond == PCOP_PRECOND_IDEAL || (o->time_cols == 0 && !fp32));
     if (L.by_modes) L.ends = take(L, mode_ends_bytes(g, fp32));
   }

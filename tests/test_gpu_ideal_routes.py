@@ -1,6 +1,6 @@
 """The ideal preconditioner's two routes: with an explicit dst_kernel the
 sequential substitution runs on the sine-transform kernels that were asked for,
-with dst_kernel = 0 the recurrences by modes.
+with dst_kernel = 0 the recurrences by modes (from two levels on, nx > 127).
 
 Both are backward stable solves of the same systems: 1e-12 of the oracle's, and
 1e-5 with FP32 transforms, as in the other tests of this preconditioner."""
@@ -36,6 +36,22 @@ def test_ideal_honours_dst_kernel(dim, nx, nt, batch, dst_kernel, precision):
     w, names = families(s, torch.tensor(v, device=DEV))
     assert ("modes" in names) == (dst_kernel == 0)
     assert ("ideal_step" in names) == (dst_kernel != 0)
+    tol = 1e-5 if precision == "mixed" else 1e-12
+    for b, gm in enumerate(gammas):
+        wo = P.IdealRBD(D.make_problem(dim, nx, nt, gm)).apply(v[b].ravel())
+        assert np.linalg.norm(w[b].cpu().numpy().ravel() - wo) <= tol * np.linalg.norm(wo)
+
+
+@pytest.mark.parametrize("dim,nx,nt,batch", [(2, 255, 2, 1), (2, 511, 2, 2), (2, 127, 2, 1), (2, 255, 3, 1)])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_ideal_of_one_level_is_one_solve(dim, nx, nt, batch, precision):
+    gammas = [10.0 ** (-2 - 3 * b) for b in range(batch)]
+    print(f"ideal of few levels {precision} {dim} {nx} {nt} {batch}", flush=True)
+    s = Solver(dim, nx, nt, gammas, precision=precision, side="flexible" if precision == "mixed" else "right",
+               precond="ideal", restart=1, device=DEV)
+    v = W.random_vector(dim, nx, nt, seed=32, batch=batch)
+    w, names = families(s, torch.tensor(v, device=DEV))
+    assert ("ideal_step" in names) == (nt == 2 and nx > 127)
     tol = 1e-5 if precision == "mixed" else 1e-12
     for b, gm in enumerate(gammas):
         wo = P.IdealRBD(D.make_problem(dim, nx, nt, gm)).apply(v[b].ravel())
