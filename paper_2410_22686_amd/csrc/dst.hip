@@ -33,9 +33,9 @@ struct DivideParams {
   const double* mu1;     // [nx] 1-D eigenvalues (4/h^2) sin^2(pi k h/2)
   const double* lam;     // [2K] (re, im) of lambda_k
   const double* alpha;   // [B]
-  const int* active;     // [B] or null
+  const int* active;     // [B] or null: planes of members without it are skipped
   double cnorm;
-  int spm;               // slices per member: plane p belongs to member p / spm, slice p mod spm
+  int spm;               // planes per member: plane p belongs to member p / spm, with the division slice p mod spm
   const double* im1;     // [nx] 1/m_k of the Q1 mass matrix, or null (M = I): the shifted
                          // operator sigma M + tau K has the sine-basis eigenvalues
                          // prod_d m_{k_d} (sigma + tau sum_d k_{k_d}/m_{k_d}), mu1 holding k/m
@@ -52,7 +52,7 @@ __global__ void __launch_bounds__(NT) dst_lines_kernel(Geo g, cx<T>* __restrict_
   const long long plane = blk / tiles;
   const int l0 = (int)(blk - plane * tiles) * LINES;
   const long long pbase = plane * lg.plane_stride;
-  if (DIVIDE && dp.active) {
+  if (dp.active) {
     if (!dp.active[(int)(plane / dp.spm)]) return;
   }
   for (int t = threadIdx.x; t < LINES * N; t += NT) {
@@ -210,7 +210,7 @@ __global__ void __launch_bounds__(reg_threads(L)) dst_reg_kernel(Geo g, cx<T>* _
   const long long plane = blk / tiles;
   const int l0 = (int)(blk - plane * tiles) * LPB;
   const long long pbase = plane * lg.plane_stride;
-  if (DIVIDE && dp.active) {
+  if (dp.active) {
     if (!dp.active[(int)(plane / dp.spm)]) return;
   }
   const int lid = threadIdx.x / TL;
@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(NT) dst_col_kernel(Geo g, cx<T>* __restrict__ 
   // tiles blk, blk + G, ...: consecutive logical blocks sit on one XCD and
   // process neighbouring tiles (which share 128-byte lines) at the same time
   auto next = [&](long long blk) {
-    if (DIVIDE && dp.active)
+    if (dp.active)
       while (blk < total && !dp.active[(int)((blk / tiles) / dp.spm)]) blk += gridDim.x;
     return blk;
   };
@@ -397,7 +397,7 @@ __global__ void __launch_bounds__(NT) dst_half_kernel(Geo g, cx<T>* __restrict__
   const int t = threadIdx.x - lid * TM;
   cx<T>* lbuf = buf + lid * LD;
   auto next = [&](long long blk) {
-    if (DIVIDE && dp.active)
+    if (dp.active)
       while (blk < total && !dp.active[(int)((blk / tiles) / dp.spm)]) blk += gridDim.x;
     return blk;
   };
@@ -737,6 +737,8 @@ template <class T>
 static bool dst_solve(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm, const double* lam,
                       hipStream_t st) {
   const DivideParams dp{tb.mu1, lam, tb.alpha, tb.active, dst_norm(g), spm, tb.im1};
+  DivideParams all = dp;
+  all.active = nullptr;
   const cx<T>* twL = dst_twiddles<T>(tb);
   const SliceLines sl = slice_lines(g, (long long)g.B * spm);
   // every pass reads and writes the slices of the counted members once
@@ -745,7 +747,7 @@ static bool dst_solve(const Geo& g, cx<T>* spec, const PrecondTables& tb, int sp
   auto run = [&](const LineGeom& lg, bool r, bool dv, int fam) {
     if (!ok) return;
     tbeg(tb.timer, fam, pass_bytes);
-    ok = dst_pass<T>(g, spec, lg, r, dv, twL, dp, tb.dst_variant, tb.ncu, st);
+    ok = dst_pass<T>(g, spec, lg, r, dv, twL, dv ? dp : all, tb.dst_variant, tb.ncu, st);
     tend(tb.timer);
   };
   run(sl.rows, true, false, KF_DST_ROWS);
@@ -757,15 +759,17 @@ static bool dst_solve(const Geo& g, cx<T>* spec, const PrecondTables& tb, int sp
 }
 
 // the sine transform along one strided axis (2 or 3) of the nslices slices at
-// data, in place and unnormalised (dst_norm)
+// data (as many of each member), in place and unnormalised (dst_norm); those of
+// members that are switched off stay as they are
 template <class T>
 static bool dst_axis(const Geo& g, cx<T>* data, const PrecondTables& tb, long long nslices, int axis, hipStream_t st) {
-  const DivideParams dp{tb.mu1, nullptr, nullptr, nullptr, 1.0, 1, nullptr};
   const SliceLines sl = slice_lines(g, nslices);
   const bool last = axis == g.dim;
+  const LineGeom& lg = last ? sl.last : sl.ax2;
+  const DivideParams dp{tb.mu1, nullptr, nullptr, tb.active, 1.0, (int)(lg.nplanes / g.B), nullptr};
   tbeg(tb.timer, last ? KF_DST_LAST : KF_DST_AX2,
        2.0 * sizeof(cx<T>) * (double)nslices / g.B * tb.nact * g.m);
-  const bool ok = dst_pass<T>(g, data, last ? sl.last : sl.ax2, false, false, dst_twiddles<T>(tb), dp, tb.dst_variant, tb.ncu, st);
+  const bool ok = dst_pass<T>(g, data, lg, false, false, dst_twiddles<T>(tb), dp, tb.dst_variant, tb.ncu, st);
   tend(tb.timer);
   return ok;
 }
