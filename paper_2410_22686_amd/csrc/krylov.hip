@@ -784,9 +784,11 @@ void launch_set_scale(const double* red, int col, int B, double* sc, double* nor
   set_scale_kernel<<<(B + 63) / 64, 64, 0, st>>>(red, col, B, sc, norm, active);
 }
 
-// Blocks per member of the block kernels over nv basis vectors: at most one
-// chunk of 128 values per block, and over all members about as many as keep
-// 10000 chunks of 1 KB in flight (40 KB per CU).  Fewer leave the memory idle,
+// Blocks per member of the block kernels over nv basis vectors with B members
+// running: at least one chunk of 128 values per block, and over all of them
+// about as many as keep 10000 chunks of 1 KB in flight (40 KB per CU; counted
+// over the members of the batch instead, the last member of 64 ran its passes
+// on 32 blocks: 46.8 ms per solve instead of 18.6, 2-D nx = 127, n = 63, V-cycles).  Fewer leave the memory idle,
 // more only spread the accesses: at 2.1 GB vectors and S = 4 the multi-dot
 // ran, with 512 / 1024 / 2048 blocks, 3.3 / 5.5 / 5.4 TB/s at nv = 1,
 // 6.6 / 6.7 / 6.2 at nv = 9 and 7.1 / 6.7 / 6.4 at nv = 20, the update

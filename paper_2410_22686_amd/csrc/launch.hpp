@@ -227,7 +227,7 @@ constexpr int kBlockRecNorm = kBlockMax * kBlockCol;
 constexpr int kBlockRecSkip = kBlockRecNorm + kBlockMax;
 constexpr int kBlockRecB = kBlockRecSkip + 1;
 constexpr int kBlockRec = kBlockRecB + kBlockMax * kBlockMax + 3;
-constexpr int kBlockGrid = 2048;  // most blocks over all members
+constexpr int kBlockGrid = 2048;  // most blocks over all running members
 int block_grid(long long vl, int B, int nv, int S);
 void launch_block_mdot(const KrylovArgs& ka, int nv, int S, double* part, int nblk, hipStream_t st);
 void launch_block_update(const KrylovArgs& ka, int nv, int S, const double* coef, const double* beta, double* part,

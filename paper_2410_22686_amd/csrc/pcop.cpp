@@ -236,7 +236,7 @@ void plan_layout(const pcop_problem* p, const pcop_options* o, Layout& L) {
   L.active = take(L, sizeof(int) * B);
   L.finish = take(L, sizeof(int) * B);
   L.hcol = take(L, sizeof(double) * B * (kMaxBasis + 1));
-  L.nblk_blk = block_grid(L.vl, B, 1, 2);  // the most of any basis size
+  L.nblk_blk = block_grid(L.vl, 1, 1, 2);  // the most of any basis size and number of running members
   L.bcoef = take(L, sizeof(double) * B * kBlockMax * kMaxBasis);
   L.bbeta = take(L, sizeof(double) * B * kBlockMax * kBlockMax);
   L.bred = take(L, sizeof(double) * B * kBlockRed);
@@ -1537,9 +1537,10 @@ pcop_status enqueue_operator(pcop_ctx c, int j, int l, int S, int n_active) {
   return s;
 }
 
-// blocks per member of the block kernels, within the caller's krylov_blocks
-int block_count(pcop_ctx c, int nv, int S) {
-  const int nb = block_grid(c->g.vl, c->g.B, nv, S);
+// blocks per member of the block kernels with nact members running, within the
+// caller's krylov_blocks
+int block_count(pcop_ctx c, int nv, int S, int nact) {
+  const int nb = block_grid(c->g.vl, std::max(1, nact), nv, S);
   return c->opt.krylov_blocks > 0 ? std::min(nb, c->opt.krylov_blocks) : nb;
 }
 
@@ -1551,7 +1552,7 @@ void enqueue_block_again(pcop_ctx c, int j, int S, int nact, hipStream_t st) {
   int* skip = c->at<int>(L.skip);
   double* red = c->at<double>(L.bred);
   double* part = c->at<double>(L.bpart);
-  const int nb = block_count(c, j + 1, S);
+  const int nb = block_count(c, j + 1, S, nact);
   KrylovArgs ka = c->kargs(c->basis(0), active);
   tbeg(c->kt(), KF_UPDATE, 8.0 * (j + 1 + 2 * S) * c->g.vl * nact);
   launch_block_update(ka, j + 1, S, c->at<double>(L.bcoef), c->at<double>(L.bbeta), part, nb, skip, st);
@@ -1583,7 +1584,7 @@ pcop_status enqueue_block(pcop_ctx c, int j, int S, bool full, int n_active, hip
     double* coef = c->at<double>(L.bcoef);
     double* beta = c->at<double>(L.bbeta);
     double* rec = c->at<double>(L.brec);
-    const int nv = j + 1, nb = block_count(c, nv, S);
+    const int nv = j + 1, nb = block_count(c, nv, S, n_active);
     tbeg(c->kt(), KF_MDOT, 8.0 * (nv + S) * c->g.vl * n_active);
     launch_block_mdot(ka, nv, S, part, nb, st);
     tend(c->kt());
