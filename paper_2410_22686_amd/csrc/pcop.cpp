@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "../../include/pcop.h"
+#include "arnoldi_plan.hpp"
 #include "launch.hpp"
 
 using namespace pcop;
@@ -1666,28 +1667,26 @@ struct MemberState {
   // basis (entries 0 .. jj): basis vector jj at the start of a block, the
   // column before it inside one
   double U[kMaxBasis - 1][kMaxBasis];
-  double est_block = 1.0;  // est at the end of the block before the last
+  double before[2] = {1.0, 1.0};  // est one and two steps ago, within the cycle
 };
 
-// steps of the next block: the fewest that the members' last convergence
-// rate says are left (rounded up, the mean over the members: a step too many
-// costs an operator apply, a block too short streams the basis once more),
-// within limit
-int block_length(const std::vector<MemberState>& ms, const std::vector<int>& h_active, double rtol, int limit,
-                 int last) {
+// steps of the next block, which starts at step j of a cycle: the mean over the
+// members still running, within limit (the last of which ends the cycle)
+int block_length(const std::vector<MemberState>& ms, const std::vector<int>& h_active, double rtol, int limit, int j,
+                 bool first_cycle) {
   double need = 0.0;
   int cnt = 0;
+  // (a later cycle of a solve that took a whole one is no short solve)
+  const int cap = first_cycle && j < 2 ? first_block(rtol, limit) : limit;
   for (size_t m = 0; m < ms.size(); ++m) {
     if (!h_active[m]) continue;
     const MemberState& s = ms[m];
-    double r = limit;
-    if (last > 0 && s.est > rtol && s.est < s.est_block)
-      r = std::min<double>(limit, std::ceil(last * std::log(s.est / rtol) / std::log(s.est_block / s.est)));
-    need += r;
+    const int k = std::min(j, 2);
+    need += k > 0 ? steps_left(s.est, s.before[k - 1], k, rtol, cap) : cap;
     ++cnt;
   }
   if (cnt == 0) return limit;
-  return std::max(1, std::min(limit, (int)std::ceil(need / cnt)));
+  return std::max(1, std::min(cap, (int)std::ceil(need / cnt)));
 }
 
 // solve the upper-triangular k x k system of the rotated Hessenberg
@@ -1787,8 +1786,10 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
   do_norm2(c, bb, nullptr, B, red + (size_t)B * kRedStride);
 
   bool first_cycle = true;
+  int cycle = 0;
   pcop_status result = PCOP_OK;
   while (true) {
+    ++cycle;
     int n_active = 0;
     for (int m = 0; m < B; ++m) n_active += ms[m].active ? 1 : 0;
     if (n_active == 0) break;
@@ -1838,11 +1839,10 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
 
     for (int m = 0; m < B; ++m) {
       h_sc[(size_t)m * kMaxBasis] = h_norm[m] > 0.0 ? 1.0 / h_norm[m] : 0.0;
-      ms[m].est_block = ms[m].est;
+      ms[m].before[0] = ms[m].before[1] = ms[m].est;
     }
 
     int j = 0;
-    int last = 0;                   // steps of the block before, 0 at the start of a cycle
     int limit = block_limit(c);     // 1 once a block had to be cut
     while (j < restart) {
       n_active = 0;
@@ -1851,7 +1851,7 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
         n_active += h_active[m];
         if (h_active[m]) left = std::min(left, std::max(1, maxit - ms[m].iters));
       }
-      const int S = block_length(ms, h_active, rtol, std::min(limit, left), last);
+      const int S = block_length(ms, h_active, rtol, std::min(limit, left), j, cycle == 1);
       int cnt = S;
       if (use_graph) {
         // a chunk of Arnoldi steps as one graph, whole blocks of it; members
@@ -1911,8 +1911,7 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
           if (!(col[j + l + 1] > kBlockMinRatio * before)) cnt = std::min(cnt, l + 1);
         }
       }
-      const bool cut = cnt % S != 0;
-      if (cut) limit = 1;
+      if (cnt % S != 0) limit = 1;
       // Givens rotations of the new columns; a member ends its cycle at the
       // first step that converges, exhausts maxit or reaches the restart
       bool any_finish = false;
@@ -1935,7 +1934,6 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
               const double* before = column(m, jj - 1);
               for (int i = 0; i <= jj; ++i) ms_.U[jj][i] = before[i];
             }
-            if ((jj - j) % S == 0) ms_.est_block = ms_.est;
             // Op u = u - w where the step stored w = u - Op u
             if (block_shifted(c, (jj - j) % S, S)) {
               for (int i = 0; i <= jj; ++i) col[i] = ms_.U[jj][i] - col[i];
@@ -1962,6 +1960,8 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
           ms_.gv[jj + 1] = -sth * ms_.gv[jj];
           ms_.gv[jj] = cth * ms_.gv[jj];
           ms_.iters += 1;
+          ms_.before[1] = ms_.before[0];
+          ms_.before[0] = ms_.est;
           ms_.est = std::fabs(ms_.gv[jj + 1]) / ms_.beta0;
           if (res_hist && ms_.iters <= maxit) res_hist[(size_t)m * (maxit + 1) + ms_.iters] = ms_.est;
           const bool conv = ms_.est <= rtol || bsub == 0.0;
@@ -1976,7 +1976,6 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
           }
         }
       }
-      last = cut ? cnt % S : S;
       j += cnt;
       if (!any_finish) continue;
       // form the correction for the members that end their cycle here
