@@ -600,12 +600,11 @@ __global__ void __launch_bounds__(kWave) mg_sweep_columns_kernel(int nx, int m, 
 // correction where the first level's residual was, which its restriction has
 // consumed.  Operations per point as in the kernels above.
 // What bounds it is latency: one block per slice, a barrier per phase.  One
-// apply, 64 slices, before and now: 2-D nx = 63 FP64 red-black 78 -> 54 us,
-// lexicographic 248 -> 83, symmetric 472 -> 129; with 16 times the slices
-// (FP64, one block per CU) 260 -> 261, 473 -> 380, 845 -> 565; 3-D nx = 15,
-// two members, 69 -> 58, 141 -> 99, 253 -> 167.
+// apply, 64 slices, level by level and so: 2-D nx = 63 FP64 red-black 98 -> 55
+// us, lexicographic 246 -> 82, symmetric 478 -> 129; 3-D nx = 15 66 -> 53,
+// 121 -> 97, 216 -> 169 (tail_level says where it is taken).
 // ---------------------------------------------------------------------------
-constexpr int kTailThreads = 512;
+constexpr int kTailThreads = 512;  // at most
 constexpr size_t kTailLds = 160 * 1024 - 1024;
 
 template <class T>
@@ -632,13 +631,13 @@ __global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, con
   cx<T>* r = base + m0;
   cx<T>* znext = base + m0;
   cx<T>* rnext = base + 2 * m0;
-  for (int i = tid; i < m0; i += kTailThreads) r[i] = rin[(size_t)s * m0 + i];
+  for (int i = tid; i < m0; i += (int)blockDim.x) r[i] = rin[(size_t)s * m0 + i];
   __syncthreads();
   for (int l = 0; l < lv.levels; ++l) {
     const int nx = lv.nx[l], m = points(nx);
     const T* __restrict__ coef = lv.coef[l];
     if (smoother == 0) {
-      for (int i = tid; i < m; i += kTailThreads) {
+      for (int i = tid; i < m; i += (int)blockDim.x) {
         int c[3];
         coords(i, nx, DIM, c);
         cx<T> acc = r[i];
@@ -672,7 +671,7 @@ __global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, con
         for (int st = 0; st <= top; ++st) {
           const int w = pass ? top - st : st;
           const int x3lo = max(0, w - 2 * (nx - 1)), x3hi = min(w, nx - 1);
-          for (int t = tid; t < (x3hi - x3lo + 1) * nx; t += kTailThreads) {
+          for (int t = tid; t < (x3hi - x3lo + 1) * nx; t += (int)blockDim.x) {
             const int x3 = x3lo + t / nx, x1 = t % nx, x2 = w - x3 - x1;
             if (x2 < 0 || x2 >= nx) continue;
             const int c[3] = {x1, x2, x3};
@@ -694,7 +693,7 @@ __global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, con
     __syncthreads();
     if (l + 1 == lv.levels) break;
     // residual over the consumed right-hand side (red-black: the red points)
-    for (int i = tid; i < m; i += kTailThreads) {
+    for (int i = tid; i < m; i += (int)blockDim.x) {
       int c[3];
       coords(i, nx, DIM, c);
       cx<T> acc{0, 0};
@@ -716,7 +715,7 @@ __global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, con
     }
     __syncthreads();
     const int nxc = lv.nx[l + 1], mc = points(nxc);
-    for (int I = tid; I < mc; I += kTailThreads) {
+    for (int I = tid; I < mc; I += (int)blockDim.x) {
       int C[3];
       coords(I, nxc, DIM, C);
       cx<T> acc{0, 0};
@@ -741,7 +740,7 @@ __global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, con
   for (int l = lv.levels - 2; l >= 0; --l) {
     const int nx = lv.nx[l], m = points(nx), nxc = lv.nx[l + 1];
     cx<T>* zf = l == 0 ? base : z - m;
-    for (int i = tid; i < m; i += kTailThreads) {
+    for (int i = tid; i < m; i += (int)blockDim.x) {
       int f[3];
       coords(i, nx, DIM, f);
       int ci[DIM][2];
@@ -774,20 +773,41 @@ __global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, con
     __syncthreads();
     z = zf;
   }
-  for (int i = tid; i < m0; i += kTailThreads) out[(size_t)s * m0 + i] = base[i];
+  for (int i = tid; i < m0; i += (int)blockDim.x) out[(size_t)s * m0 + i] = base[i];
 }
 
 // first level of the one-launch coarse end: its two planes and the coarser
-// right-hand sides fit LDS, and a 2-D column per lane
+// right-hand sides fit LDS, and a 2-D column per lane.  Where that is one block
+// per CU (FP64 2-D nx = 63, 3-D nx = 15) the slices run in rounds of one per
+// CU, each a chain of barriers; a level by itself runs on all slices at once.
+// The red-black sweep has no chain to shorten and is faster by itself on any
+// number of slices, the lexicographic ones from some rounds on.  In this launch
+// against by itself, FP64, us per apply: 64 slices red-black 3-D nx = 15 53 /
+// 47, 2-D nx = 63 55 / 50, lexicographic 97 / 103, 82 / 98, symmetric 169 /
+// 185, 129 / 169; 512 slices lexicographic 247 / 206, 192 / 187, symmetric 413
+// / 335, 286 / 319; 2048 slices 870 / 701, 726 / 629, 1477 / 1197, 1106 / 1120.
 template <class T, int DIM>
-static int tail_level(const PrecondTables& tb, size_t* lds) {
+static int tail_level(const PrecondTables& tb, int slices, size_t* lds) {
   for (int l = 0; l < tb.mg_levels; ++l) {
     size_t pts = tb.mg[l].m;
     for (int k = l; k < tb.mg_levels; ++k) pts += tb.mg[k].m;
     *lds = pts * sizeof(cx<T>);
-    if (*lds <= kTailLds && tb.mg[l].nx <= kWave) return l;
+    if (*lds > kTailLds || tb.mg[l].nx > kWave) continue;
+    if (2 * *lds > kTailLds && (tb.mg_smoother == 0 || slices > (DIM == 3 ? 1 : 4) * (long long)tb.ncu)) continue;
+    return l;
   }
   return tb.mg_levels;
+}
+
+// threads of a block whose first level has m points.  With a block per CU and
+// fewer the most, whose idle waves cost nothing; beyond, waves that only meet
+// barriers keep other slices out (FP64 red-black, thousands of slices, 512
+// threads against these: 2-D nx = 7 127 -> 45 us, nx = 15 197 -> 117, nx = 31
+// 218 -> 188; symmetric 274 -> 102, 519 -> 246, 543 -> 366; 3-D nx = 7 285 ->
+// 185).
+static int tail_threads(long long m, int slices, int ncu) {
+  if (slices <= ncu || m > 1024) return kTailThreads;
+  return m > 256 ? 256 : m > 64 ? 128 : 64;
 }
 
 // slices per thread of the smoother, the residual and the prolongation on
@@ -830,7 +850,7 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
   };
   // levels from lt on in one launch (one point at the latest)
   size_t tail_lds = 0;
-  const int lt = tail_level<T, DIM>(tb, &tail_lds);
+  const int lt = tail_level<T, DIM>(tb, slices, &tail_lds);
   for (int l = 0; l < lt; ++l) {
     const int nx = tb.mg[l].nx;
     const int m = (int)tb.mg[l].m;
@@ -899,8 +919,8 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     (void)lds_ok;
     tbeg(tb.timer, KF_MG_SMOOTH, 2.0 * cs * tb.mg[lt].m);
-    mg_tail_kernel<T, DIM><<<slices, kTailThreads, tail_lds, st>>>(lv, rbuf(lt), lt == 0 ? spec : zbuf(lt), sh,
-                                                                   tb.mg_smoother);
+    mg_tail_kernel<T, DIM><<<slices, tail_threads(tb.mg[lt].m, slices, tb.ncu), tail_lds, st>>>(
+        lv, rbuf(lt), lt == 0 ? spec : zbuf(lt), sh, tb.mg_smoother);
     tend(tb.timer);
   }
   for (int l = lt - 1; l >= 0; --l) {
