@@ -20,6 +20,9 @@
 // host with a at the level's face midpoints.  Coefficients per level:
 // coef[0][i] = tau diag, coef[1 + 2a][i] / coef[2 + 2a][i] = tau times the
 // minus / plus neighbour along axis a (zero where the neighbour is outside).
+#include <atomic>
+#include <cstdint>
+
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -787,16 +790,35 @@ __global__ void __launch_bounds__(kTailThreads) mg_tail_kernel(MgTail<T> lv, con
 // 185, 129 / 169; 512 slices lexicographic 247 / 206, 192 / 187, symmetric 413
 // / 335, 286 / 319; 2048 slices 870 / 701, 726 / 629, 1477 / 1197, 1106 / 1120.
 template <class T, int DIM>
-static int tail_level(const PrecondTables& tb, int slices, size_t* lds) {
+static int tail_level(const PrecondTables& tb, int slices, size_t most, size_t* lds) {
   for (int l = 0; l < tb.mg_levels; ++l) {
     size_t pts = tb.mg[l].m;
     for (int k = l; k < tb.mg_levels; ++k) pts += tb.mg[k].m;
     *lds = pts * sizeof(cx<T>);
-    if (*lds > kTailLds || tb.mg[l].nx > kWave) continue;
+    if (*lds > most || tb.mg[l].nx > kWave) continue;
     if (2 * *lds > kTailLds && (tb.mg_smoother == 0 || slices > (DIM == 3 ? 1 : 4) * (long long)tb.ncu)) continue;
     return l;
   }
   return tb.mg_levels;
+}
+
+// LDS that the coarse end's blocks may take on the current device: more than 64
+// KB has to be asked for once on each
+template <class T, int DIM>
+static size_t tail_lds_limit() {
+  constexpr size_t kPlain = 64 * 1024;
+  static std::atomic<uint64_t> granted{0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return kPlain;
+  const uint64_t bit = dev < 64 ? uint64_t(1) << dev : 0;
+  if (granted.load() & bit) return kTailLds;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&mg_tail_kernel<T, DIM>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+    (void)hipGetLastError();
+    return kPlain;
+  }
+  granted.fetch_or(bit);
+  return kTailLds;
 }
 
 // threads of a block whose first level has m points.  With a block per CU and
@@ -850,7 +872,7 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
   };
   // levels from lt on in one launch (one point at the latest)
   size_t tail_lds = 0;
-  const int lt = tail_level<T, DIM>(tb, slices, &tail_lds);
+  const int lt = tail_level<T, DIM>(tb, slices, tail_lds_limit<T, DIM>(), &tail_lds);
   for (int l = 0; l < lt; ++l) {
     const int nx = tb.mg[l].nx;
     const int m = (int)tb.mg[l].m;
@@ -915,9 +937,6 @@ static void mg_cycle(const Geo& g, cx<T>* spec, const PrecondTables& tb, int spm
       lv.nx[l - lt] = tb.mg[l].nx;
       lv.coef[l - lt] = coefp(l);
     }
-    static const hipError_t lds_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&mg_tail_kernel<T, DIM>),
-                                                         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    (void)lds_ok;
     tbeg(tb.timer, KF_MG_SMOOTH, 2.0 * cs * tb.mg[lt].m);
     mg_tail_kernel<T, DIM><<<slices, tail_threads(tb.mg[lt].m, slices, tb.ncu), tail_lds, st>>>(
         lv, rbuf(lt), lt == 0 ? spec : zbuf(lt), sh, tb.mg_smoother);
