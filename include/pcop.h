@@ -119,7 +119,8 @@ typedef struct {
  *              (needs a non-default stream), 0: plain launches.
  *   graph_chunk Arnoldi steps per graph launch when graph = 1 (>= 1; whole
  *              blocks of up to four steps that are orthogonalised together, so
- *              at least one block).
+ *              at least one block).  Shorter blocks before the end, and steps
+ *              with half of the members stopped, are plain launches.
  *   reorth_tol a second Gram-Schmidt pass is run for a member when the
  *              coefficients of the new vector against the basis exceed
  *              reorth_tol times its norm (0 = always, < 0 = never).

@@ -1,6 +1,6 @@
-// How many Arnoldi steps the next block of a solve takes (host code without
-// device calls).  A step too many costs an operator apply, a block too short
-// streams the basis once more.
+// How many Arnoldi steps the next block of a solve takes, and which of them are
+// replayed as graphs (host code without device calls).  A step too many costs
+// an operator apply, a block too short streams the basis once more.
 #pragma once
 
 #include <algorithm>
@@ -24,6 +24,22 @@ inline int first_block(double rtol, int limit) { return std::min(limit, rtol >= 
 inline int steps_left(double est, double before, int k, double rtol, int limit) {
   if (!(est > rtol && est < before)) return limit;
   return (int)std::max(1.0, std::min<double>(limit, std::ceil(k * std::log(est / rtol) / std::log(before / est))));
+}
+
+// Steps from step j of a cycle on that one captured graph holds, 0 where the
+// block of S steps is launched plainly.  full: the solve's longest block, first:
+// its first_block, chunk: graph_chunk.  Graphs hold whole blocks at fixed
+// places -- every G steps (the blocks that fit chunk, one at least) from the
+// start of a cycle or behind a short first block -- so a context stores at most
+// 2 ceil(restart / G) + 1 of them, whatever the data.  Block lengths follow the convergence seen;
+// captured wherever they led, a right-hand side that converged otherwise met
+// captures (some 0.1 ms each) inside its solve.
+inline int graph_steps(int j, int S, int full, int first, int chunk, int restart) {
+  if (j == 0 && S == first && first < full) return S;
+  const int G = full * std::max(1, chunk / full);
+  const bool placed = j % G == 0 || (first < full && j > 0 && (j - first) % G == 0);
+  if (S != full || !placed || j + full > restart) return 0;
+  return full * std::max(1, std::min(chunk, restart - j) / full);
 }
 
 }  // namespace pcop

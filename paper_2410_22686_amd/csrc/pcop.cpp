@@ -1853,11 +1853,16 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
       }
       const int S = block_length(ms, h_active, rtol, std::min(limit, left), j, cycle == 1);
       int cnt = S;
-      if (use_graph) {
-        // a chunk of Arnoldi steps as one graph, whole blocks of it; members
-        // that converge inside the chunk run to its end and their extra steps
-        // are ignored
-        cnt = S * std::max(1, std::min(c->opt.graph_chunk, restart - j) / S);
+      // a chunk of Arnoldi steps as one graph, whole blocks of it; members that
+      // converge inside the chunk run to its end and their extra steps are
+      // ignored.  A graph's reductions are laid out for the whole batch: with
+      // half of it stopped plain launches give the rest more blocks
+      const int gsteps = use_graph && 2 * n_active > B
+                             ? graph_steps(j, S, block_limit(c), first_block(rtol, block_limit(c)), c->opt.graph_chunk, restart)
+                             : 0;
+      const bool as_graph = gsteps > 0;
+      if (as_graph) {
+        cnt = gsteps;
         hipGraphExec_t ge = nullptr;
         pcop_status gs = chunk_graph(c, j, cnt, S, &ge);
         if (gs != PCOP_OK) return gs;
@@ -1896,7 +1901,7 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
       // the measured column jj of member m and, inside a block, the norm of
       // its vector before the Gram-Schmidt pass
       auto column = [&](int m, int jj) -> const double* {
-        if (use_graph) return &h_H[(size_t)m * H_member + (size_t)jj * H_ld];
+        if (as_graph) return &h_H[(size_t)m * H_member + (size_t)jj * H_ld];
         if (S > 1) return &h_rec[(size_t)m * kBlockRec + (size_t)(jj - j) * kBlockCol];
         return &h_col[(size_t)m * (kMaxBasis + 1)];
       };
@@ -1907,7 +1912,7 @@ extern "C" pcop_status pcop_solve(pcop_ctx c, const double* b, double* x, int tr
         for (int m = 0; m < B; ++m) {
           if (!h_active[m]) continue;
           const double* col = column(m, j + l);
-          const double before = use_graph ? col[kHld - 1] : h_rec[(size_t)m * kBlockRec + kBlockRecNorm + l];
+          const double before = as_graph ? col[kHld - 1] : h_rec[(size_t)m * kBlockRec + kBlockRecNorm + l];
           if (!(col[j + l + 1] > kBlockMinRatio * before)) cnt = std::min(cnt, l + 1);
         }
       }
