@@ -337,6 +337,15 @@ def _compose_cpu(cfg, iters, pb, t_start, threads, cores, t_mv, n_mv, t_dft, m_d
     }
 
 
+def precond_route(stats):
+    """How a leg's preconditioner ran, by the timed families.  By modes there
+    are no time passes: kernel_choice then names what they would take."""
+    for family, route in (("time_fwd", "time transforms"), ("ideal_step", "step by step"), ("modes", "by modes")):
+        if family in stats:
+            return route
+    return None
+
+
 def precond_stats(stats, precision, cfg):
     """The preconditioner's passes (time forward, spatial solves, time
     inverse; or the passes by modes) of one leg: their algorithmic bytes over
@@ -526,7 +535,8 @@ def main():
             "solves_per_s": round(n_solves / leg_s[leg], 4), "ms_per_solve": round(1e3 * leg_s[leg] / n_solves, 3),
             "precision": opts_of[leg]["precision"], "krylov": f"{opts_of[leg]['side']} GMRES(30)",
             "iters": [i.iters for i in infos[leg]], "relres_true": [i.relres_true for i in infos[leg]],
-            "kernel_choice": solvers[leg].kernels, "kernels": kernel_table(stats_of[leg]),
+            "preconditioner": precond_route(stats_of[leg]), "kernel_choice": solvers[leg].kernels,
+            "kernels": kernel_table(stats_of[leg]),
             "kernel_table_source": "eager solve after the timed region" if opts_of[leg]["graph"] else "timed region",
         }
     mixed_vs_fp64 = None

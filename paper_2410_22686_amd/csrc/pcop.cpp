@@ -495,6 +495,28 @@ void do_norm2(pcop_ctx c, const double* w, const int* mask, int nact, double* ou
   launch_reduce_partials(c->at<double>(c->L.partial), c->nb_mdot[0], 1, c->g.B, out, c->st);
 }
 
+// Krylov vectors per block: the longest run of operator applies without an
+// orthogonalisation in between (krylov.hip).  Rounding in the operator and in
+// the Gram-Schmidt pass counts relative to the share of a vector that the pass
+// leaves.  With the shift of block_shifted that share was 1e-3 to 0.06 at worst
+// over four steps, for gamma from 1e-10 to 1, and the iterates agree with
+// single steps to 1e-15 (as two orders of summation do); without it to 1e-14
+// over four and three times less over two steps, so the left side, where the
+// shift would cost passes of its own, takes two.  FP32 V-cycles agree to 4e-13.
+// The FP32 sine transforms are exact solves but for their rounding, which then
+// sets the last steps of a solve to 1e-8 (two-step blocks moved those
+// residuals by up to a quarter): single steps.
+int block_limit(pcop_ctx c) {
+  if (c->fp32 && c->opt.spatial == PCOP_DST) return 1;
+  return c->opt.side == PCOP_LEFT ? 2 : kBlockMax;
+}
+
+// Whether step l of a block of S stores u - Op u instead of Op u.  The
+// preconditioned spectrum lies around 1 (Re = 1 for the ideal preconditioner),
+// so this takes the vector's own direction out of what the next step applies
+// the operator to, for one more read in the matvec (its residual form).
+bool block_shifted(pcop_ctx c, int l, int S) { return c->opt.side != PCOP_LEFT && l + 1 < S; }
+
 // ---------------------------------------------------------------------------
 // kernel autotuner: times every candidate pair (time-pass kernels, sine-
 // transform kernels) of the preconditioner on the context's stream and keeps
@@ -516,7 +538,7 @@ struct TuneResult {
 // new one, so separate processes (a benchmark and a profiler run) run the
 // same kernels.  Lines of another version, malformed lines and entries that
 // do not fit the context are ignored (the shape is then tuned afresh).
-constexpr int kTuneVersion = 2;  // bump when the meaning of a kernel choice changes
+constexpr int kTuneVersion = 3;  // bump when the kernels behind a choice, or what is timed, change
 using TuneKey = std::pair<std::string, std::array<int, 14>>;
 std::mutex g_tune_mu;
 std::map<TuneKey, TuneResult> g_tune_cache;
@@ -606,7 +628,7 @@ pcop_status tune_kernels(pcop_ctx c) {
   PCOP_HIP(hipGetDevice(&dev));
   const TuneKey key{device_id(dev),
                     {g.dim, g.nx, g.n, g.B, (int)c->fp32, c->opt.spatial, c->opt.time_cols, c->opt.dst_kernel,
-                     c->coeff_kind + 2 * c->mass, c->opt.precond, c->opt.kkt_jchunk, c->opt.krylov_blocks,
+                     c->coeff_kind + 2 * c->mass + 4 * (c->opt.side == PCOP_LEFT), c->opt.precond, c->opt.kkt_jchunk, c->opt.krylov_blocks,
                      c->opt.gs_update, c->opt.restart}};
   const char* env = std::getenv("PCOP_TUNE_CACHE");
   const std::string cache_file = (env && *env) ? env : "";
@@ -697,16 +719,19 @@ pcop_status tune_kernels(pcop_ctx c) {
     }
     if (err != hipSuccess) break;
   }
-  // matvec: time levels per thread
+  // matvec: the applies of one block of Arnoldi steps, which take the residual
+  // form but for the last (block_shifted): levels per block of the LDS-tiled
+  // kernel (the built-in choice first), then levels per thread of the
+  // one-thread-per-point kernel
   double best_kkt = 1e300;
-  // levels per block of the LDS-tiled kernel (the built-in choice first), then
-  // levels per thread of the one-thread-per-point kernel
+  const int S = block_limit(c);
   for (int jc : {c->kkt_jchunk, -8, -16, -32, 16, 1, 2, 4, 8, 32}) {
     if (err != hipSuccess || c->opt.kkt_jchunk != 0) break;
     double ms = 0;
     if (!time_it([&] {
-          launch_kkt_apply(g, v, w, nullptr, c->at<double>(c->L.alpha), nullptr, 0, nullptr, false, c->ecoef,
-                           c->ediag, c->eoff, jc, st);
+          for (int l = 0; l < S; ++l)
+            launch_kkt_apply(g, v, w, block_shifted(c, l, S) ? v : nullptr, c->at<double>(c->L.alpha), nullptr, 0,
+                             nullptr, false, c->ecoef, c->ediag, c->eoff, jc, st);
         }, ms))
       break;
     if (better(ms, best_kkt)) {
@@ -1490,31 +1515,9 @@ pcop_status pcop_timing_read(pcop_ctx c, pcop_kernel_stat* out, int cap, int* co
 // ---------------------------------------------------------------------------
 namespace {
 
-// Krylov vectors per block: the longest run of operator applies without an
-// orthogonalisation in between (krylov.hip).  Rounding in the operator and in
-// the Gram-Schmidt pass counts relative to the share of a vector that the pass
-// leaves.  With the shift of block_shifted that share was 1e-3 to 0.06 at worst
-// over four steps, for gamma from 1e-10 to 1, and the iterates agree with
-// single steps to 1e-15 (as two orders of summation do); without it to 1e-14
-// over four and three times less over two steps, so the left side, where the
-// shift would cost passes of its own, takes two.  FP32 V-cycles agree to 4e-13.
-// The FP32 sine transforms are exact solves but for their rounding, which then
-// sets the last steps of a solve to 1e-8 (two-step blocks moved those
-// residuals by up to a quarter): single steps.
-int block_limit(pcop_ctx c) {
-  if (c->fp32 && c->opt.spatial == PCOP_DST) return 1;
-  return c->opt.side == PCOP_LEFT ? 2 : kBlockMax;
-}
-
 // A vector is used only while the ratio of the one before it stays above
 // this; below it the block is cut and the cycle goes on in single steps.
 constexpr double kBlockMinRatio = 1e-6;
-
-// Whether step l of a block of S stores u - Op u instead of Op u.  The
-// preconditioned spectrum lies around 1 (Re = 1 for the ideal preconditioner),
-// so this takes the vector's own direction out of what the next step applies
-// the operator to, for one more read in the matvec (its residual form).
-bool block_shifted(pcop_ctx c, int l, int S) { return c->opt.side != PCOP_LEFT && l + 1 < S; }
 
 // w = Op u (or u - Op u, block_shifted) for Krylov step j + l of the block
 // of S that starts at j: u is basis vector j (l = 0) or the vector w of the
