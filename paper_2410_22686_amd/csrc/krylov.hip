@@ -289,7 +289,7 @@ __global__ void set_scale_kernel(const double* __restrict__ red, int col, int B,
 // in between, sit in the basis slots nv .. nv + S - 1 (nv = j + 1) and are
 // orthogonalised together, so the basis is streamed once per S steps by each
 // of the two passes instead of once per step.  The Arnoldi steps of a solve
-// then move about 2 j + 4 S + 2 vectors per S steps instead of S (2 j + 5).
+// then move 2 j + 3 S + 2 vectors per S steps instead of S (2 j + 5).
 //
 // What bounds both passes is HBM.  One thread cannot hold the (nv + ..) S
 // partial products of S = 4 (over 160 doubles at 40 basis vectors), so the

@@ -386,9 +386,11 @@ __global__ void __launch_bounds__(plane_threads(L)) mode_plane_out_kernel(Geo g,
 // neighbouring modes and splits their steps into CH chunks: each thread runs
 // its chunk from zero to get the value it passes on, the values are chained
 // through LDS and closed with eps, and a second run from its carry writes the
-// result (the second read comes from the caches on the shapes that take this
-// kernel).  CH = 1 where the modes alone fill the chip, else 16, so that a
-// short mode list is not a serial walk through memory.
+// result.  The second read comes from the caches where the slices fit the last
+// level (256 MB), as those of most shapes that take this kernel do; beyond (2-D
+// nx = 63, n = 299, 17 members: 323 MB; nx = 255, n = 511, one member: 531 MB)
+// it is a third pass over memory.  CH = 1 where the modes alone fill the chip,
+// else 16, so that a short mode list is not a serial walk through memory.
 // ---------------------------------------------------------------------------
 constexpr int kScanAhead = 8;  // loads in flight per thread
 template <class T, int CH>
@@ -672,7 +674,8 @@ __global__ void __launch_bounds__(NT) mode_march_out_kernel(Geo g, cx<T>* __rest
 // ---------------------------------------------------------------------------
 // Chunks of the marching passes, 0 where whole passes are taken: enough blocks
 // for two rounds of the chip (1024), chunks of at least 8 steps (a chunk's end
-// and start values are two more slices each).
+// and start values are two more slices each), at most 16 of them (2-D nx = 255
+// takes them from two members on, nx = 127 from eight).
 static int march_chunks(const Geo& g) {
   if (g.dim == 2 && g.nx <= 63) return 0;  // no axis left beyond the planes
   const int M = g.nx + 1, lpb = 256 / (M / 8);
@@ -735,7 +738,7 @@ static bool modes_L(const Geo& g, const double* v, double* w, cx<T>* c, cx<T>* e
     const bool axis = !PLANES || g.dim == 3;  // a last axis beyond the planes
     if (axis && !launch_dst_axis(g, c, fp32, tb, nslices, g.dim == 3 ? 3 : 2, st)) return false;
     tbeg(tb.timer, KF_MODES, pass);
-    // 64 waves' worth of modes per XCD and more need no split in time
+    // 128 waves of modes per XCD and more need no split in time
     if ((long long)g.m * g.B >= 65536)
       mode_scan_kernel<T, 1><<<dim3((g.m + 255) / 256, g.B), 256, 0, st>>>(g, c, mp);
     else
