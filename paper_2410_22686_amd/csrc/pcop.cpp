@@ -1680,7 +1680,7 @@ int block_length(const std::vector<MemberState>& ms, const std::vector<int>& h_a
   double need = 0.0;
   int cnt = 0;
   // (a later cycle of a solve that took a whole one is no short solve)
-  const int cap = first_cycle && j < 2 ? first_block(rtol, limit) : limit;
+  const int cap = first_cycle && j < kShortSteps ? first_block(rtol, limit) : limit;
   for (size_t m = 0; m < ms.size(); ++m) {
     if (!h_active[m]) continue;
     const MemberState& s = ms[m];

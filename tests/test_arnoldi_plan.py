@@ -46,7 +46,7 @@ int main() {
             }
           }
           const int G = full > chunk ? full : chunk / full * full;
-          if ((int)graphs.size() > 2 * ((restart + G - 1) / G) + 1) return fail("too many graphs", full, first, chunk, restart);
+          if ((int)graphs.size() > 2 * ((restart + G - 1) / G) + kShortSteps) return fail("too many graphs", full, first, chunk, restart);
           // a solve of full blocks runs as graphs from its start to the last
           // whole block of the cycle
           int j = 0;
@@ -54,7 +54,9 @@ int main() {
             const int S = j == 0 ? first : full;
             if (j + S > restart) break;
             const int g = graph_steps(j, S, full, first, chunk, restart);
-            if (g == 0) return fail("plain block", full, first, chunk, restart);
+            if (g == 0 || (j < kShortSteps && j % first == 0 && j + first <= restart &&
+                           graph_steps(j, first, full, first, chunk, restart) == 0 && first < full))
+              return fail("plain block", full, first, chunk, restart);
             j += g;
           }
         }

@@ -36,3 +36,19 @@ def test_few_steps_few_applies(nx, nt, side, gamma, rtol):
         pb = D.make_problem(2, nx, nt, gamma)
         bo = b.cpu().numpy().ravel()
         assert np.linalg.norm(bo - D.kkt_scaled(pb) @ x.cpu().numpy().ravel()) <= 1.05 * rtol * np.linalg.norm(bo)
+
+
+def test_residual_that_falls_late():
+    """Three steps to 1e-3, the third of which brings most: the rate of the
+    first two says many more are left, and the next block has two steps at
+    most."""
+    nx, nt = 255, 256
+    g, f, y0 = W.smooth_fields(2, nx, nt)
+    s = Solver(2, nx, nt, 1e-4, rtol=1e-3, restart=20, device=DEV)
+    b = s.rhs(*(torch.tensor(t[None], device=DEV) for t in (g, f, y0)))
+    s.timing_enable(True)
+    _, infos, hist = s.solve(b, history=True)
+    steps = s.timing_read()["kkt_apply"]["launches"] - 2
+    s.timing_enable(False)
+    print(f"iterations {infos[0].iters} steps {steps} residuals {hist[0, :5]}", flush=True)
+    assert infos[0].converged and steps <= infos[0].iters + 1
