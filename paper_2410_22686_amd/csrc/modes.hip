@@ -433,12 +433,13 @@ __global__ void __launch_bounds__(256) mode_scan_kernel(Geo g, cx<T>* __restrict
   if (CH > 1 || mp.eps != 0.0) {
     ends[q][k] = walk(z, [](int, cx<double>) {});
     __syncthreads();
-    // chunk p passes on ends + d^{-its length} times what it got
-    const double decay = mode_decay(delta, len);
+    // chunk p passes on ends + d^{-its length} times what it got: whole chunks,
+    // then one of the rest, then empty ones that pass on what they get
+    const int whole = n / len, rest = n - whole * len;
+    const double decay = mode_decay(delta, len), drest = rest > 0 ? mode_decay(delta, rest) : 1.0;
     auto chain = [&](cx<double> a, int upto) {
-      for (int p = 0; p < upto; ++p) {
-        const int lp = max(0, min(n - p * len, len));
-        const double dp = lp == len ? decay : mode_decay(delta, lp);
+      for (int p = 0; p < min(upto, whole + (rest > 0)); ++p) {
+        const double dp = p < whole ? decay : drest;
         a = cx<double>{ends[p][k].x + dp * a.x, ends[p][k].y + dp * a.y};
       }
       return a;
